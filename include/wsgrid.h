@@ -150,8 +150,8 @@ int grid_plan_info(const wsg_plan* plan, int* Nprime, int* n_layers, int* t_lo,
  * Device workspace (bytes) for one grid_visibilities or degrid_visibilities
  * call with M visibilities at precision `prec` that holds every w-layer at
  * once: the w-layer stack (n_layers N'^2 complex; only tiles some visibility
- * reaches are touched), the FFT intermediate before and after its transpose
- * (2 n_layers N N' complex), the binned visibility records (2 M records), the
+ * reaches are touched), the FFT intermediate (n_layers N N' complex, N
+ * rounded up to a multiple of 16), the binned visibility records (2 M records), the
  * degrid per-tile parts (8 M complex) and the bin tables.  0 on a bad argument.
  */
 size_t grid_workspace_bytes(const wsg_plan* plan, wsg_prec prec, int64_t M);
@@ -344,7 +344,7 @@ int64_t grid_last_skipped(const wsg_plan* plan);
  *   1 grid 3-D scatter tiles                     5 degrid FFT pass along p (+ w-screen)
  *   2 grid FFT pass along v (+ crop)             6 degrid FFT pass along q
  *   3 grid FFT pass along u (+ w-screen, sum)    7 degrid 3-D gather tiles
- *   8 grid intermediate transpose                9 degrid intermediate transpose
+ *   8, 9 kept for the intermediate's transposes, which the library no longer makes
  * grid_prepare's binning is timed as stage 4 (it is the degridding binning).
  * wsg_stage_times() waits for the recorded events, writes the summed
  * milliseconds and the number of timed sections of the first n stages (one per

@@ -44,6 +44,13 @@ __device__ __forceinline__ void phase_turns(double f, double* s, double* c) {
     sincospi(2.0 * r, s, c);
 }
 
+// Orders this wave's LDS accesses around a hand-over between its lanes.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // One binned visibility.  ruv packs the first support index along u (low 16
 // bits) and v (high 16 bits), both taken modulo N'; rt is the first support
 // layer counted from t_lo.  nu are the fractional offsets in [-1/2, 1/2).
@@ -74,6 +81,7 @@ struct DevParams {
     // layer pass: virtual layers [pl0, pl0 + pln) (pl0 a multiple of kTileT)
     // sit in the stack and FFT buffers, local layer index t - pl0
     int pl0, pln;
+    int classes;            // pass_a_classes(Np)
     double umul;            // l_max / x0: u -> u'
     double nscale;          // w -> w'
     double zshift;          // (1 - n0) / n_scale: z = (n - 1) / n_scale + zshift
@@ -82,6 +90,72 @@ struct DevParams {
 };
 
 constexpr int kTileR = 16, kTileS = 16, kTileT = 16;
+
+// Words of the marks of one row of nbs tiles.
+__host__ __device__ constexpr int mask_words(int nbs) { return (nbs + 31) / 32; }
+
+// Classes of outputs that FFT pass A splits a line of N' cells into (the
+// transforms inside a class have at most 1024 points, without a factor 3).
+__host__ __device__ constexpr int pass_a_classes(int Np) {
+    const int p2 = Np % 3 == 0 ? Np / 3 : Np;
+    return (Np % 3 == 0 ? 3 : 1) * (p2 > 1024 ? p2 / 1024 : 1);
+}
+
+// Pass A's twiddle table behind the plan's Np roots of unity: for an F-point
+// transform (F = Np / classes = 2^a) the twiddles W_(16 n)^(k m) of each pass in
+// the order its lanes read them, [m][k < n] (n: points joined before the pass):
+// 16 x 16 for the second radix-16 pass, then those of the last pass of radix
+// 2, 4 or 8; then the class twiddles W_Np^(n b), [b][n < F].
+__host__ __device__ constexpr int log2_floor(int n) {
+    int l = 0;
+    while ((2 << l) <= n) ++l;
+    return l;
+}
+struct PassATable {
+    int F, second, last_radix, last_n, entries;     // entries without the class twiddles
+};
+__host__ __device__ constexpr PassATable pass_a_table(int Np) {
+    const int F = Np / pass_a_classes(Np), l = log2_floor(F), rem = l % 4;
+    const int second = l >= 8 ? 256 : 0, radix = rem ? 1 << rem : 0, n = rem ? F / radix : 0;
+    return {F, second, radix, n, second + radix * n};
+}
+
+// Cells of one layer of a tile as the degrid direction stores them: class by
+// class (cell s of a line is of class s mod C), the 16 rows of the class's cells
+// of the tile each, so that a pass A block, which holds one class of the tile's
+// rows, writes contiguous pieces.
+// first class output a (cell s = C a + c) of v tile bs
+__host__ __device__ constexpr int tile_class_first(int bs, int c, int C) { return (kTileS * bs - c + C - 1) / C; }
+// cells of class c per row of v tile bs
+__host__ __device__ constexpr int tile_class_cells(int bs, int c, int C) {
+    return tile_class_first(bs + 1, c, C) - tile_class_first(bs, c, C);
+}
+// place of cell s of row r within its tile's layer
+template <int C>
+__device__ __forceinline__ int degrid_cell(int s, int r) {
+    const int c = s % C, bs = s / kTileS;
+    int before = 0;
+    for (int k = 0; k < c; ++k) before += tile_class_cells(bs, k, C);
+    return before * kTileR + r * tile_class_cells(bs, c, C) + s / C - tile_class_first(bs, c, C);
+}
+// its inverse: the row r and the cell s of place e of v tile bs
+__device__ __forceinline__ void degrid_place(int e, int bs, int C, int& r, int& s) {
+    int c = 0, n = tile_class_cells(bs, 0, C);
+    while (e >= n * kTileR) {
+        e -= n * kTileR;
+        n = tile_class_cells(bs, ++c, C);
+    }
+    r = e / n;
+    s = C * (tile_class_first(bs, c, C) + e % n) + c;
+}
+
+// The intermediate between the FFT passes: [t][q / 16][r / 16][16 q][16 r].
+__host__ __device__ constexpr int inter_blocks(int N) { return (N + 15) / 16; }     // blocks of image rows q
+
+// Index of the tile (br, bs) of layer tl of the pass among the pass's tile layers.
+__device__ __forceinline__ size_t tile_base(const DevParams& P, int tl, int br, int bs) {
+    return (size_t(tl) * P.nbr + br) * P.nbs + bs;
+}
 
 // blockIdx -> logical block so that each XCD (blocks are dealt round-robin to
 // the 8 XCDs) walks a contiguous range of logical blocks.  For uniform work

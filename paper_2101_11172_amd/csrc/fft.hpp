@@ -15,6 +15,13 @@ namespace wsg {
 
 // LDS index with one pad element per 16 (spreads the radix-16 scatter over banks).
 __device__ __forceinline__ int lpad(int i) { return i + (i >> 4); }
+// lpad(i + D k) with pi = lpad(i): for D a multiple of 16 a constant offset from
+// pi (an address immediate once k is one), which the compiler does not find.
+template <int D>
+__device__ __forceinline__ int lpad_at(int i, int pi, int k) {
+    if constexpr (D % 16 == 0) return pi + (D + D / 16) * k;
+    else return lpad(i + D * k);
+}
 template <int N>
 struct LinePad {
     static constexpr int size = N + N / 16;
@@ -138,12 +145,13 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
     constexpr int T = N / 16;
     constexpr int P16 = LOG2 / 4;
     constexpr int REM = LOG2 % 4;
+    const int pj = lpad(j);
     int Ns = 1;
 #pragma unroll
     for (int p = 0; p < P16; ++p) {
         if (p > 0) {
 #pragma unroll
-            for (int m = 0; m < 16; ++m) v[m] = buf[lpad(j + m * T)];
+            for (int m = 0; m < 16; ++m) v[m] = buf[lpad_at<T>(j, pj, m)];
             const int k = j & (Ns - 1);
             const int stride = N / (Ns * 16);
 #pragma unroll
@@ -152,22 +160,21 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
         dft16<R, DIR>(v);
         if (!R3 && REM == 0 && p == P16 - 1) return;   // natural order: v[m] = X[j + m T]
         __syncthreads();
-        const int base = (j / Ns) * Ns * 16 + (j & (Ns - 1));
+        const int base = (j / Ns) * Ns * 16 + (j & (Ns - 1)), pb = lpad(base);
 #pragma unroll
-        for (int m = 0; m < 16; ++m) buf[lpad(base + m * Ns)] = v[m];
+        for (int m = 0; m < 16; ++m) buf[p == 0 ? pb + m : pb + m * (Ns + Ns / 16)] = v[m];     // lpad(base + m Ns)
         __syncthreads();
         Ns *= 16;
     }
     if constexpr (REM > 0) {
         constexpr int RR = 1 << REM;      // radix of this pass
-        constexpr int B = 16 / RR;        // butterflies per thread
-        constexpr int NR = N / RR;        // butterfly stride (= Ns when this is the last pass)
+        constexpr int B = 16 / RR;        // butterflies per thread, N / RR apart (Ns in the last pass)
         constexpr int TWS = R3 ? 3 : 1;   // N / (Ns RR)
         cpx<R> u[16];
 #pragma unroll
         for (int b = 0; b < B; ++b)
 #pragma unroll
-            for (int m = 0; m < RR; ++m) u[b * RR + m] = buf[lpad(j + b * T + m * NR)];
+            for (int m = 0; m < RR; ++m) u[b * RR + m] = buf[lpad_at<T>(j, pj, b + m * B)];      // j + b T + m NR
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             const int k = (j + b * T) & (Ns - 1);
@@ -215,7 +222,62 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
         }
         __syncthreads();
 #pragma unroll
-        for (int m = 0; m < 16; ++m) v[m] = buf[lpad(j + m * T)];
+        for (int m = 0; m < 16; ++m) v[m] = buf[lpad_at<T>(j, pj, m)];
+    }
+}
+
+// FFT of one line of F = 2^a <= 1024 points held by T = F/16 lanes of one wave:
+// the passes of fft_line without block barriers.  Twiddles come in the order the
+// lanes read them (pass_a_table): those of the second radix-16 pass from LDS
+// (tab), those of the last pass from memory (last).
+template <typename R, int F, int DIR>
+__device__ __forceinline__ void fft_wave(cpx<R> (&v)[16], cpx<R>* buf, const cpx<R>* tab,
+                                         const cpx<R>* __restrict__ last, int j) {
+    constexpr int LOG2 = log2_of<F>(), T = F / 16, P16 = LOG2 / 4, REM = LOG2 % 4;
+    static_assert((1 << LOG2) == F && F >= 16 && F <= 1024 && P16 <= 2, "F = 2^a in [16, 1024]");
+    auto turn = [](cpx<R> a, cpx<R> w) {
+        if (DIR < 0) w.y = -w.y;
+        return cmul(a, w);
+    };
+    const int pj = lpad(j);
+    dft16<R, DIR>(v);
+    if constexpr (LOG2 == 4) return;
+    wave_sync();
+#pragma unroll
+    for (int m = 0; m < 16; ++m) buf[17 * j + m] = v[m];               // lpad(16 j + m)
+    wave_sync();
+    if constexpr (P16 == 2) {
+#pragma unroll
+        for (int m = 0; m < 16; ++m) v[m] = buf[lpad_at<T>(j, pj, m)];
+        const int k = j & 15;
+#pragma unroll
+        for (int m = 1; m < 16; ++m) v[m] = turn(v[m], tab[m * 16 + k]);
+        dft16<R, DIR>(v);
+        if constexpr (REM == 0) return;
+        wave_sync();
+        const int base = (j / 16) * 272 + k;                           // lpad of (j / 16) 256 + k
+#pragma unroll
+        for (int m = 0; m < 16; ++m) buf[base + m * 17] = v[m];
+        wave_sync();
+    }
+    if constexpr (REM > 0) {
+        constexpr int RR = 1 << REM, B = 16 / RR, NR = F / RR;
+        cpx<R> u[16];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+#pragma unroll
+            for (int m = 0; m < RR; ++m) u[b * RR + m] = buf[lpad_at<T>(j, pj, b + m * B)];      // j + b T + m NR
+#pragma unroll
+            for (int m = 1; m < RR; ++m) u[b * RR + m] = turn(u[b * RR + m], last[m * NR + j + b * T]);
+            if constexpr (RR == 2) dft2<R, DIR>(u[b * RR], u[b * RR + 1]);
+            if constexpr (RR == 4) dft4<R, DIR>(u[b * RR], u[b * RR + 1], u[b * RR + 2], u[b * RR + 3]);
+            if constexpr (RR == 8) dft8<R, DIR>(&u[b * RR]);
+        }
+        // output X[j + b T + m NR] = X[j + T (b + m B)]
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int m = 0; m < RR; ++m) v[b + m * B] = u[b * RR + m];
     }
 }
 

@@ -13,7 +13,7 @@ bool fft_supported(int Np) {
     }
 }
 
-template bool launch_fft<float>(bool, const DevParams&, const uint8_t*, const uint8_t*, cpx<float>*, cpx<float>*,
-                                cpx<float>*, const cpx<float>*, const float*, const float*, float*, hipStream_t);
+template bool launch_fft<float>(bool, const DevParams&, const uint32_t*, const uint8_t*, cpx<float>*, cpx<float>*,
+                                const cpx<float>*, const float*, const float*, float*, hipStream_t);
 
 }  // namespace wsg

@@ -451,9 +451,11 @@ __global__ void __launch_bounds__(256) k_bin_local_sort(const Rec<R>* __restrict
 // per-bin sort).  Only marked tiles of the stack are written (grid) or filled
 // (degrid); the FFT passes treat unmarked tiles as zero (grid) or skip them
 // (degrid).  A row of tiles (t tile, u tile) is marked in `rows` when one of
-// its tiles is (`rows` zero on entry; racing stores all write 1).
+// its tiles is (`rows` zero on entry; racing stores all write 1), and its tiles
+// are bits of the row's words of `mask` (mask_words(nbs) words, zero on entry).
 static __global__ void k_tile_occupancy(const uint32_t* __restrict__ start, const uint32_t* __restrict__ cls, DevParams P,
-                                 uint8_t* __restrict__ occ, uint8_t* __restrict__ rows, uint32_t* __restrict__ flag) {
+                                 uint8_t* __restrict__ occ, uint8_t* __restrict__ rows, uint32_t* __restrict__ mask,
+                                 uint32_t* __restrict__ flag) {
     const int tile = blockIdx.x * blockDim.x + threadIdx.x;
     const int nt = P.nch * P.nbt * P.nbs * P.nbr;
     if (tile >= nt) return;
@@ -478,7 +480,10 @@ static __global__ void k_tile_occupancy(const uint32_t* __restrict__ start, cons
     }
     occ[tile] = any ? 1 : 0;
     flag[tile] = any ? 1u : 0u;
-    if (any) rows[bt * P.nbr + br] = 1;
+    if (any) {
+        rows[bt * P.nbr + br] = 1;
+        atomicOr(&mask[size_t(bt * P.nbr + br) * mask_words(P.nbs) + (bs >> 5)], 1u << (bs & 31));
+    }
 }
 
 // The occupied tiles in tile order: list[pos[t]] = t for every marked tile t,
@@ -618,13 +623,6 @@ __device__ __forceinline__ void record_weights(const Rec<R>& r, const R* __restr
         wv[a] = hv;
         if (a < WZ) wt[a] = ht;
     }
-}
-
-// Orders this wave's LDS accesses around a hand-over between its lanes.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ float bits_to_word(int v, float) { return __int_as_float(v); }
@@ -932,7 +930,7 @@ __global__ void __launch_bounds__((ScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles
     // write the tile: rows of kTileS cells
     for (int i = tid; i < nt_valid * kTileR * kTileS; i += NT) {
         const int ss = i % kTileS, rr = (i / kTileS) % kTileR, tt = i / (kTileR * kTileS);
-        stack[((size_t)(t0 - P.pl0 + tt) * P.Np + (r0 + rr)) * P.Np + (s0 + ss)] = cpx<R>{tre[i], tim[i]};
+        stack[tile_base(P, t0 - P.pl0 + tt, br, bs) * (kTileR * kTileS) + rr * kTileS + ss] = cpx<R>{tre[i], tim[i]};
     }
 }
 
@@ -1003,13 +1001,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     }
     for (int i = tid; i < G::kLen; i += 256) {
         const int c = i - G::kGuard;
-        cpx<R> q{R(0), R(0)};
-        if (c >= 0 && c < G::kCells) {
-            const int tt = c / G::kLT, rem = c % G::kLT, rr = rem / G::kLR, ss = rem % G::kLR;
-            if (tt < nt_valid && rr < kTileR && ss < kTileS)
-                q = stack[((size_t)(t0 - P.pl0 + tt) * P.Np + (r0 + rr)) * P.Np + (s0 + ss)];
-        }
-        g[i] = q;
+        const int tt = c / G::kLT, rem = c % G::kLT, rr = rem / G::kLR, ss = rem % G::kLR;
+        if (c < 0 || tt >= nt_valid || rr >= kTileR || ss >= kTileS) g[i] = cpx<R>{R(0), R(0)};
+    }
+    // the tile's cells, in the order pass A stored them, one of each layer per thread
+    {
+        int rr, ss;
+        degrid_place(tid, bs, P.classes, rr, ss);
+        const cpx<R>* src = stack + tile_base(P, t0 - P.pl0, br, bs) * (kTileR * kTileS) + tid;
+        const size_t layer = size_t(P.nbr) * P.nbs * (kTileR * kTileS);
+        cpx<R>* dst = g + G::kGuard + rr * G::kLR + ss - s0;
+#pragma unroll 4
+        for (int tt = 0; tt < nt_valid; ++tt) dst[tt * G::kLT] = src[tt * layer];
     }
     __syncthreads();
 
@@ -1094,10 +1097,11 @@ __global__ void k_degrid_finish(const Rec<R>* __restrict__ rec, const uint32_t* 
 
 // --------------------------------------------------------------- FFT passes --
 //
-// Stack layout [t][r][s] (s fastest).  Every FFT pass reads and writes whole
-// lines: grid writes [t][r][q] and reads [t][q][r], degrid writes [t][q][r] and
-// reads [t][r][q], with k_transpose in between (q is the image row).  Image
-// rows j <-> q and columns i <-> p.  The FFT output bin
+// The stack is tiled: [t][u tile][v tile][16 x 16 cells], [r][s] within a tile
+// in the grid direction (tile_elems).  Pass A transforms along s and writes
+// (reads, in the degrid direction) the intermediate [t][q][r] in segments of
+// 16 consecutive r, pass B transforms its whole lines along r (q is the image
+// row).  Image rows j <-> q and columns i <-> p.  The FFT output bin
 // f of a line maps to image index (f + N/2) mod N' and is kept when below N
 // (Algorithm 5 step 3c); the degrid input places image index p at bin
 // (p - N/2) mod N' (zero padding, Algorithm 6 step 3b).
@@ -1112,9 +1116,6 @@ struct FftCfg {
     // FP64 at 384 threads measured 28 % slower)
     static constexpr int kNLr =
         (T >= 256) ? 1 : (N % 3 == 0 && T < 384 && sizeof(R) == 4) ? 384 / T : 256 / T;
-    // lines per block for the tile-row passes: a power of two dividing the 16
-    // rows of a row of tiles
-    static constexpr int kNLt = kNLr >= 16 ? 16 : kNLr >= 8 ? 8 : kNLr >= 4 ? 4 : kNLr >= 2 ? 2 : 1;
 };
 
 // (f + N/2) mod N' for a bin f < N' (image index of FFT bin f, or the bin of
@@ -1125,61 +1126,186 @@ __device__ __forceinline__ int shift_half(int f, int half) {
     return q >= NP ? q - NP : q;
 }
 
-// grid pass A: IFFT along s of stack rows [t][r][:], keep image rows q, write
-// the lines [t][r][q] (transposed afterwards by k_transpose).  One block per
-// layer and row of tiles (kTileR stack rows, taken NL at a time); the next NL
-// rows are loaded while the current ones are transformed.  Unmarked tiles are
-// read as zero; a row of tiles with none marked is neither transformed nor
-// written (its lines are zero).  Layer t of the pass is virtual layer
-// t + t_base; in a batched call (chl = the channels' layer stride, else 0) a
-// padding layer (virtual layer mod chl >= n_layers) is skipped.
+// Pass A splits a line of N' = C F cells into C classes of outputs (f = C a + b
+// for class b), each an F-point transform of F <= 1024 points:
+//     X[C a + b] = sum_n W_F^(n a) W_N'^(n b) sum_m x[n + F m] W_C^(m b).
+// A block holds kRows lines of a row of tiles at one class, a line per T = F/16
+// lanes of one wave (no block barrier inside a transform), so that the lines fit
+// in its registers and LDS and leave transposed, in segments of kRows
+// frequencies r: no pass over the intermediate is spent on transposing it.  The
+// classes of a line read the same inputs, which their blocks share in the L2.
+// Bound by latency and VALU issue (about half of the issue slots are used, two
+// blocks of 8 waves per CU).  Wide field (N' = 4096, 49 layers, one pass), with
+// the transpose of the intermediate that a whole-line pass needs: FP32 grid
+// 2.13 -> 1.76 ms, degrid 2.06 -> 2.00; FP64 4.55 -> 3.49 and 4.58 -> 3.71;
+// N' = 3072 FP32 degrid 1.63 -> 0.97.  Rows are dealt to the XCDs in turn: the
+// marked rows thin out towards the upper layers, and with a contiguous range of
+// rows per XCD the grid direction took 2.90 ms.  At kRows = 16 (one block of
+// 1024 threads per CU) FP32 took 2.99 ms.  Twiddles gathered from the table of
+// N' roots instead of pass_a_table's order cost 0.65 ms.
 template <typename R, int NP>
-__global__ void __launch_bounds__((FftCfg<R, NP>::kNLt * FftCfg<R, NP>::T))
-    k_grid_fft_a(const cpx<R>* __restrict__ stack, const uint8_t* __restrict__ occ, cpx<R>* __restrict__ inter,
+struct PassACfg {
+    static constexpr int kClasses = pass_a_classes(NP);
+    static constexpr int F = NP / kClasses, T = F / 16;
+    // two blocks per CU: at most 512 threads of 128 registers (FP32) or 256 of 256 (FP64), 80 KB of LDS
+    static constexpr int kMost = sizeof(R) == 8 ? 256 : 512;
+    static constexpr int kRows = 16 * T <= kMost ? 16 : kMost / T;
+    static constexpr int kHalves = kTileR / kRows;               // blocks per row of tiles and class
+    static constexpr int kThreads = kRows * T;
+    static constexpr int kWaves = kThreads < kMost ? 1 : sizeof(R) == 8 ? 2 : 4;     // per SIMD, as two full blocks hold
+    static_assert(T <= 64 && 64 % T == 0 && (F & (F - 1)) == 0, "a line's lanes lie in one wave");
+    // line stride in LDS: the transposed accesses of kRows lines meet distinct banks
+    static constexpr int kBanks = 256 / int(sizeof(cpx<R>));
+    static constexpr int LP = (LinePad<F>::size + kBanks - 1) / kBanks * kBanks + (kBanks >= kRows ? kBanks / kRows : 1);
+};
+
+// grid pass A: IFFT along s of kRows lines of a row of tiles for one class,
+// image rows q kept, written to the intermediate.  The marked tiles of the row
+// (about a fifth of them at wide field) are listed and only they are read; a row
+// of tiles with none marked is neither transformed nor written (pass B reads it
+// as zeros).  Layer t of the pass is virtual layer t + t_base; in a batched call
+// (chl = the channels' layer stride, else 0) a padding layer (virtual layer mod
+// chl >= n_layers) is skipped.
+template <typename R, int NP>
+__global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((amdgpu_waves_per_eu(PassACfg<R, NP>::kWaves)))
+    k_grid_fft_a(const cpx<R>* __restrict__ stack, const uint32_t* __restrict__ mask, cpx<R>* __restrict__ inter,
                  const cpx<R>* __restrict__ tw, int N, int n_layers, int chl, int nbr, int t_base) {
-    using C = FftCfg<R, NP>;
-    constexpr int Np = C::N, T = C::T, NL = C::kNLt, LP = LinePad<Np>::size, NG = kTileR / NL;
-    static_assert(kTileR % NL == 0, "a row of tiles is a whole number of line groups");
-    __shared__ cpx<R> buf[NL * LP];
-    const int rows = Np / kTileR;
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int t = lb / rows, rt = lb % rows;
+    using A = PassACfg<R, NP>;
+    constexpr int C = A::kClasses, F = A::F, T = A::T, RW = A::kRows, LP = A::LP, NB = NP / kTileS, TH = A::kThreads;
+    constexpr int MW = mask_words(NB), PART = RW * kTileS;       // cells of a tile in the block
+    // G groups of PART threads (or one of fewer, Q cells each) share out the cells n = s mod F
+    // by their tile n / 16 mod G
+    constexpr int G = T >= 16 ? T / 16 : 1, Q = T >= 16 ? 1 : 16 / T, EG = F / kTileS / G * C;
+    constexpr PassATable TB = pass_a_table(NP);
+    __shared__ cpx<R> buf[RW * LP];
+    __shared__ cpx<R> tab[TB.second > 0 ? TB.second : 1];
+    __shared__ uint16_t list[G * EG];
+    // the tiles' twiddles, where two blocks still fit in a CU's LDS with them
+    constexpr bool TURNS = sizeof(R) == 4 || G * EG <= 384;
+    __shared__ cpx<R> tile_turn[TURNS ? G * EG : 1];
+    __shared__ int count[G];
+    int lb = xcd_interleave<A::kHalves * C>(blockIdx.x, gridDim.x);
+    const int b = lb % C;
+    lb /= C;
+    const int h = lb % A::kHalves;
+    lb /= A::kHalves;
+    const int rt = lb % nbr, t = lb / nbr;
     if (chl > 0 && (t + t_base) % chl >= n_layers) return;     // padding layer of a channel (block-uniform)
-    const int line = threadIdx.x / T, j = threadIdx.x % T;
-    cpx<R>* lbuf = buf + line * LP;
-    // tile (t / 16, s / 16, rt) holds s = j + T k
-    const uint8_t* orow = occ + (size_t)((t + t_base) / kTileT) * (Np / kTileS) * nbr + rt;
-    bool on[16], any = false;
+    const uint32_t* mrow = mask + size_t(((t + t_base) / kTileT) * nbr + rt) * MW;     // the row's marked tiles
+    uint32_t any = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        on[k] = orow[(size_t)((j + T * k) / kTileS) * nbr] != 0;
-        any = any || on[k];
-    }
-    cpx<R>* dst0 = inter + ((size_t)t * Np + rt * kTileR) * N;
-    if (!__syncthreads_or(any)) return;     // zero lines: the transpose reads them as zeros
-    auto load = [&](int g, cpx<R> (&v)[16]) {
-        const cpx<R>* src = stack + ((size_t)t * Np + (rt * kTileR + g * NL + line)) * Np;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = on[k] ? src[j + T * k] : cpx<R>{R(0), R(0)};
-    };
-    const int half = N / 2;
-    cpx<R> nx[16];
-    load(0, nx);
-    for (int g = 0; g < NG; ++g) {
-        cpx<R> v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = nx[k];
-        if (g + 1 < NG) load(g + 1, nx);
-        fft_line<R, NP, +1>(v, lbuf, tw, j);
-        // bin f = j + T k holds image row q = (f + N/2) mod N', kept when below N
-        cpx<R>* dst = dst0 + (size_t)(g * NL + line) * N;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int q = shift_half<Np>(j + T * k, half);
-            if (q < N) store_stream(dst + q, v[k]);
+    for (int i = 0; i < MW; ++i) any |= mrow[i];
+    if (any == 0) return;
+    const int tid = threadIdx.x, line = tid / T, j = tid % T;
+    // each group's marked tiles, the parts m of one n / 16 together, the last of them flagged
+    {
+        constexpr int STEP = (TH < 64 ? TH : 64) / C * C;
+        const int lane = tid & 63, w = tid >> 6;
+        if (w < G) {
+            int n = 0;
+            for (int i0 = 0; i0 < EG; i0 += STEP) {
+                const int i = i0 + lane, m = i % C, bs = i / C * G + w + m * (F / kTileS);
+                const bool on = lane < STEP && i < EG && ((mrow[bs >> 5] >> (bs & 31)) & 1u);
+                const uint64_t all = __ballot(on);
+                if (on) {
+                    const bool last = ((all >> lane) >> 1 & ((1ull << (C - 1 - m)) - 1ull)) == 0ull;
+                    const int at = w * EG + n + __popcll(all & ((1ull << lane) - 1ull));
+                    list[at] = uint16_t(bs | (last ? 0x8000 : 0));
+                    if constexpr (TURNS) tile_turn[at] = tw[bs * kTileS * b % NP];
+                }
+                n += __popcll(all);
+            }
+            if (lane == 0) count[w] = n;
         }
     }
+    for (int i = tid; i < TB.second; i += TH) tab[i] = tw[NP + i];
+    for (int i = tid; i < RW * LP; i += TH) buf[i] = cpx<R>{R(0), R(0)};
+    __syncthreads();
+    // buf[r][n] = sum_m x[n + F m] W_N'^((n + F m) b): each cell of the marked
+    // tiles is read once, kBatch tiles in flight per thread; W_N'^(s b) is the
+    // tile's W_N'^(16 bs b) (wave-uniform) times the cell's W_N'^((s mod 16) b)
+    {
+        const cpx<R>* src = stack + (size_t(t) * nbr + rt) * (size_t(NB) * kTileR * kTileS) + h * PART;
+        const int g = G > 1 ? __builtin_amdgcn_readfirstlane(tid / PART) : 0, e0 = tid % PART;
+        const int n_list = __builtin_amdgcn_readfirstlane(count[g]);
+        constexpr int kBatch = 16 / Q;
+        cpx<R> acc[Q], turn[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            acc[q] = cpx<R>{R(0), R(0)};
+            turn[q] = tw[(e0 + q * TH) % kTileS * b];
+        }
+        for (int base = 0; base < n_list; base += kBatch) {
+            cpx<R> x[kBatch][Q];
+            int en[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                en[u] = base + u < n_list ? __builtin_amdgcn_readfirstlane(int(list[g * EG + base + u])) : -1;
+                if (en[u] >= 0) {
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        x[u][q] = src[size_t(en[u] & 0x7fff) * (kTileR * kTileS) + (e0 + q * TH)];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                if (en[u] < 0) break;
+                const int bs = en[u] & 0x7fff;
+                const cpx<R> w = TURNS ? tile_turn[g * EG + base + u] : tw[bs * kTileS * b % NP];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    acc[q].x += x[u][q].x * w.x - x[u][q].y * w.y;
+                    acc[q].y += x[u][q].x * w.y + x[u][q].y * w.x;
+                    if (en[u] & 0x8000) {
+                        const int e = e0 + q * TH, n = (bs * kTileS + e % kTileS) & (F - 1);
+                        buf[e / kTileS * LP + lpad(n)] = cmul(acc[q], turn[q]);
+                        acc[q] = cpx<R>{R(0), R(0)};
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    cpx<R>* lbuf = buf + line * LP;
+    const int pj = lpad(j);
+    cpx<R> v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = lbuf[lpad_at<T>(j, pj, k)];
+    fft_wave<R, F, +1>(v, lbuf, tab, tw + NP + TB.second, j);
+    // class output a is bin f = C a + b, image row (f + N/2) mod N': the kept
+    // ones are a < a0 (image rows from N/2) and a >= a1 (image rows below N/2)
+    const int half = N / 2;
+    const int a0 = (N - half - b + C - 1) / C, a1 = (NP - half - b + C - 1) / C;
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const int a = j + T * k;
+        if (a < a0 || a >= a1) lbuf[lpad_at<T>(j, pj, k)] = v[k];
+    }
+    __syncthreads();
+    // lanes over r; step T classes outputs = C T image rows
+    const int r = tid % RW, i0 = tid / RW;
+    cpx<R>* dst = inter + (size_t(t) * inter_blocks(N) * nbr + rt) * 256 + h * RW;          // block-uniform
+    auto put = [&](int a, int hi, int q0) {       // outputs a, a + T, ... < hi; a = 0 is image row q0
+        const cpx<R>* from = buf + r * LP;
+        if constexpr (C * T % 16 == 0 && T % 16 == 0) {
+            const int q = q0 + C * a;
+            uint32_t to = uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r);
+            from += lpad(a);
+            for (; a < hi; a += T, to += uint32_t(C * T / 16) * uint32_t(nbr * 256), from += T + T / 16) dst[to] = *from;
+        } else {
+            for (; a < hi; a += T) {
+                const int q = q0 + C * a;
+                dst[uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r)] = from[lpad(a)];
+            }
+        }
+    };
+    put(i0, min(a0, F), b + half);
+    if (a1 < F) put(a1 + i0, F, b + half - NP);
 }
+
+// Offset of frequency r within a row q of the intermediate.
+__device__ __forceinline__ int inter_cell(int r) { return (r >> 4) * 256 + (r & 15); }
 
 // Bit k set when frequency r = j + T k (the k-th value of thread j of a line)
 // lies in a marked row of tiles of the tile layer whose marks start at `mark`.
@@ -1230,7 +1356,7 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
     uint32_t live = 0;
     int live_layer = -1;
     for (int t = 0; t < P.pln; ++t) {
-        const cpx<R>* src = inter + ((size_t)(seg0 + t) * N + qq) * Np;
+        const cpx<R>* src = inter + ((size_t)(seg0 + t) * inter_blocks(N) + (qq >> 4)) * (P.nbr * 256) + (qq & 15) * 16;
         const int tile_layer = __builtin_amdgcn_readfirstlane((P.pl0 + seg0 + t) / kTileT);
         if (tile_layer != live_layer) {
             live_layer = tile_layer;
@@ -1238,7 +1364,7 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
         }
         cpx<R> v[16];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = (live >> k) & 1u ? src[j + T * k] : cpx<R>{R(0), R(0)};
+        for (int k = 0; k < 16; ++k) v[k] = (live >> k) & 1u ? src[inter_cell(j + T * k)] : cpx<R>{R(0), R(0)};
         fft_line<R, NP, +1>(v, lbuf, tw, j);
         const double tl = double(tloc0 + t + P.t_lo) + P.tphase;
 #pragma unroll
@@ -1310,106 +1436,113 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
                 live_layer = tile_layer;
                 live = live_mask<T>(rows + (size_t)tile_layer * P.nbr, j);
             }
-            cpx<R>* dst = inter + ((size_t)(seg0 + t) * N + q) * Np;
+            cpx<R>* dst = inter + ((size_t)(seg0 + t) * inter_blocks(N) + (q >> 4)) * (P.nbr * 256) + (q & 15) * 16;
 #pragma unroll
             for (int k = 0; k < 16; ++k)
-                if ((live >> k) & 1u) store_stream(dst + j + T * k, v[k]);
+                if ((live >> k) & 1u) store_stream(dst + inter_cell(j + T * k), v[k]);
         }
     }
 }
 
-// degrid pass A': for each layer t and frequency r: the intermediate line
-// [t][r][:] placed at its bins and zero-padded along q, FFT along q -> stack
-// row [t][r][s].  One block per layer and row of tiles (kTileR lines, taken NL
-// at a time); the next NL lines are loaded while the current ones are
-// transformed.  Only marked tiles are stored (the gather reads no other); a row
+// degrid pass A': for each layer t and frequency r: the intermediate column
+// [t][:][r] placed at its bins and zero-padded along q, FFT along q, the marked
+// tiles of the stack written (the gather reads no other); class b holds the
+// outputs s = C a + b, which a tile stores class by class (degrid_cell).  A row
 // of tiles with none marked is skipped.  Layers and padding layers as for
 // k_grid_fft_a.
 template <typename R, int NP>
-__global__ void __launch_bounds__((FftCfg<R, NP>::kNLt * FftCfg<R, NP>::T))
-    k_degrid_fft_a(const cpx<R>* __restrict__ inter, const uint8_t* __restrict__ occ, const cpx<R>* __restrict__ tw,
+__global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((amdgpu_waves_per_eu(PassACfg<R, NP>::kWaves)))
+    k_degrid_fft_a(const cpx<R>* __restrict__ inter, const uint32_t* __restrict__ mask, const cpx<R>* __restrict__ tw,
                    cpx<R>* __restrict__ stack, int N, int n_layers, int chl, int nbr, int t_base) {
-    using C = FftCfg<R, NP>;
-    constexpr int Np = C::N, T = C::T, NL = C::kNLt, LP = LinePad<Np>::size, NG = kTileR / NL;
-    static_assert(kTileR % NL == 0, "a row of tiles is a whole number of line groups");
-    __shared__ cpx<R> buf[NL * LP];
-    const int rows = Np / kTileR;
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int t = lb / rows, rt = lb % rows;
+    using A = PassACfg<R, NP>;
+    constexpr int C = A::kClasses, F = A::F, T = A::T, RW = A::kRows, LP = A::LP, NB = NP / kTileS;
+    constexpr int MW = mask_words(NB), TE = kTileR * kTileS;
+    constexpr PassATable TB = pass_a_table(NP);
+    __shared__ cpx<R> buf[RW * LP];
+    __shared__ cpx<R> tab[TB.second > 0 ? TB.second : 1];
+    int lb = xcd_interleave<A::kHalves * C>(blockIdx.x, gridDim.x);
+    const int b = lb % C;
+    lb /= C;
+    const int h = lb % A::kHalves;
+    lb /= A::kHalves;
+    const int rt = lb % nbr, t = lb / nbr;
     if (chl > 0 && (t + t_base) % chl >= n_layers) return;     // padding layer of a channel (block-uniform)
-    const int line = threadIdx.x / T, j = threadIdx.x % T;
-    cpx<R>* lbuf = buf + line * LP;
-    const uint8_t* orow = occ + (size_t)((t + t_base) / kTileT) * (Np / kTileS) * nbr + rt;
-    bool on[16], any = false;
+    const uint32_t* mrow = mask + size_t(((t + t_base) / kTileT) * nbr + rt) * MW;
+    uint32_t mw[MW + 1], any = 0;                              // the row's marks (block-uniform)
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        on[k] = orow[(size_t)((j + T * k) / kTileS) * nbr] != 0;
-        any = any || on[k];
-    }
-    if (!__syncthreads_or(any)) return;
+    for (int i = 0; i < MW; ++i) any |= mw[i] = mrow[i];
+    mw[MW] = 0;
+    if (any == 0) return;
+    const int tid = threadIdx.x, line = tid / T, j = tid % T;
+    for (int i = tid; i < TB.second; i += A::kThreads) tab[i] = tw[NP + i];
     const int half = N / 2;
-    // thread j of a line holds bins f = j + T k; bin f carries image row
-    // q = (f + N/2) mod N' when that is below N, else zero padding
-    auto load = [&](int g, cpx<R> (&v)[16]) {
-        const cpx<R>* src = inter + ((size_t)t * Np + (rt * kTileR + g * NL + line)) * N;
+    // lanes over r: y[n] = W_N'^(-n b) sum_m x[n + F m] W_C^(-m b) of line r,
+    // n = n0 + T k; bin f = n + F m carries image row q = (f + N/2) mod N' when
+    // that is below N (f < N/2 or f >= N' - N/2)
+    const int r = tid % RW, n0 = tid / RW;
+    const cpx<R>* src = inter + (size_t(t) * inter_blocks(N) * nbr + rt) * 256 + h * RW;      // block-uniform
+    auto at = [&](int q) { return src[uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r)]; };
+    cpx<R> y[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) y[k] = cpx<R>{R(0), R(0)};
+#pragma unroll
+    for (int m = 0; m < C; ++m) {
+        if (F * m >= half && F * (m + 1) <= NP - half) continue;       // padding bins only
+        cpx<R> x[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            const int q = shift_half<Np>(j + T * k, half);
-            v[k] = q < N ? src[q] : cpx<R>{R(0), R(0)};
+            const int f0 = T * k + F * m;              // the T bins from f0 (block-uniform cases)
+            x[k] = cpx<R>{R(0), R(0)};
+            if (f0 + T <= half) {
+                x[k] = at(n0 + f0 + half);
+            } else if (f0 >= NP - half) {
+                x[k] = at(n0 + f0 + half - NP);
+            } else if (f0 < half || f0 + T > NP - half) {
+                const int q = shift_half<NP>(n0 + f0, half);
+                if (q < N) x[k] = at(q);
+            }
         }
-    };
-    cpx<R> nx[16];
-    load(0, nx);
-    for (int g = 0; g < NG; ++g) {
-        cpx<R> v[16];
+        const cpx<R> wm = tw[(m * b % C) * F];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = nx[k];
-        if (g + 1 < NG) load(g + 1, nx);
-        fft_line<R, NP, -1>(v, lbuf, tw, j);
-        cpx<R>* dst = stack + ((size_t)t * Np + (rt * kTileR + g * NL + line)) * Np;
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-            if (on[k]) dst[j + T * k] = v[k];
+        for (int k = 0; k < 16; ++k) {
+            y[k].x += x[k].x * wm.x + x[k].y * wm.y;
+            y[k].y += x[k].y * wm.x - x[k].x * wm.y;
+        }
+        __builtin_amdgcn_sched_barrier(0);     // 16 loads in flight per thread are enough, more spill
     }
-}
-
-// out[t][b][a] = in[t][a][b] for a < A, b < B, through a 64 x 64 LDS tile:
-// reads and writes are whole 64-element rows (512 B FP32) away from the edges.
-// The stack frequency r (16 per row of tiles) is the row index a of the input
-// when R_IN, else the row index b of the output.  Lines of r whose row of
-// tiles (t / 16, r / 16) is not marked in `rows` are zero on input (R_IN: not
-// read) or not needed on output (not written; a tile with none needed is
-// skipped whole).
-template <typename R, int THREADS, bool R_IN>
-__global__ void __launch_bounds__(THREADS) k_transpose(const cpx<R>* __restrict__ in, cpx<R>* __restrict__ out,
-                                                       int A, int B, const uint8_t* __restrict__ rows, int nbr,
-                                                       int t_base, int chl, int n_layers) {
-    __shared__ cpx<R> tile[64][65];
-    __shared__ uint8_t live[4];
-    const int ta_n = (A + 63) / 64, tb_n = (B + 63) / 64;
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int t = lb / (ta_n * tb_n), rem = lb % (ta_n * tb_n);
-    if (chl > 0 && (t + t_base) % chl >= n_layers) return;     // padding layer of a channel (block-uniform)
-    const int a0 = (rem / tb_n) * 64, b0 = (rem % tb_n) * 64;
-    const int r0 = R_IN ? a0 : b0;
-    if (threadIdx.x < 4)
-        live[threadIdx.x] = rows[((t + t_base) / kTileT) * nbr + min(r0 / kTileR + int(threadIdx.x), nbr - 1)];
-    __syncthreads();
-    if (!(live[0] | live[1] | live[2] | live[3])) return;
-    // only the live frequencies r are moved: the others are zero in the grid
-    // direction (the pass-B FFT reads them as zeros) and unused in the degrid
-    // direction (pass A' skips their rows)
-    const cpx<R>* src = in + (size_t)t * A * B;
-    for (int i = threadIdx.x; i < 64 * 64; i += THREADS) {
-        const int a = a0 + i / 64, b = b0 + i % 64;
-        if (a < A && b < B && live[(R_IN ? i / 64 : i % 64) / kTileR]) tile[i / 64][i % 64] = src[(size_t)a * B + b];
+    cpx<R>* lbuf = buf + line * LP;
+    const int pj = lpad(j), pn = lpad(n0);
+    const cpx<R>* turn_b = tw + NP + TB.entries + b * F;               // W_N'^(n b)
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        if (b > 0) {
+            const cpx<R> w = turn_b[n0 + T * k];
+            y[k] = cmul(y[k], cpx<R>{w.x, -w.y});
+        }
+        buf[r * LP + lpad_at<T>(n0, pn, k)] = y[k];
     }
     __syncthreads();
-    cpx<R>* dst = out + (size_t)t * A * B;
-    for (int i = threadIdx.x; i < 64 * 64; i += THREADS) {
-        const int b = b0 + i / 64, a = a0 + i % 64;
-        if (a < A && b < B && live[(R_IN ? i % 64 : i / 64) / kTileR])
-            store_stream(dst + (size_t)b * A + a, tile[i % 64][i / 64]);
+    cpx<R> v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = lbuf[lpad_at<T>(j, pj, k)];
+    fft_wave<R, F, -1>(v, lbuf, tab, tw + NP + TB.second, j);
+    cpx<R>* dst = stack + (size_t(t) * nbr + rt) * (size_t(NB) * TE);
+    if constexpr (NP % 256 == 0) {
+        // the values k of a thread are NP / 256 tiles apart, at one place within their tiles
+        constexpr int STEP = NP / 256;
+        const int s0 = C * j + b, tile0 = s0 / kTileS;
+        const uint32_t cell = uint32_t(tile0 * TE + degrid_cell<C>(s0, h * RW + line));
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t marks = uint32_t(((uint64_t(mw[STEP * k / 32 + 1]) << 32) | mw[STEP * k / 32]) >> (STEP * k % 32));
+            if ((marks >> tile0) & 1u) dst[cell + uint32_t(STEP * k * TE)] = v[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int s = C * (j + T * k) + b, tile = s / kTileS;
+            if ((mw[0] >> tile) & 1u) dst[tile * TE + degrid_cell<C>(s, h * RW + line)] = v[k];
+        }
     }
 }
 

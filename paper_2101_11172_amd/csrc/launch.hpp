@@ -36,10 +36,11 @@ bool launch_tiles(bool grid, int W, int Wz, bool same, int nblocks, const Rec<R>
 // FFT lengths N' the passes are compiled for: 2^a and 3 2^a from 64 to 8192.
 bool fft_supported(int Np);
 
-// One layer pass of the FFT stages (pass A, transpose, pass B with the
-// w-screen; or their adjoints); false when N' is not compiled.
+// One layer pass of the FFT stages (pass A, then pass B with the w-screen; or
+// their adjoints); false when N' is not compiled.  mask: the marked tiles of
+// each row of tiles, rows: whether a row has any.
 template <typename R>
-bool launch_fft(bool grid, const DevParams& P, const uint8_t* occ, const uint8_t* rows, cpx<R>* stack, cpx<R>* inter,
-                cpx<R>* inter2, const cpx<R>* tw, const R* corr, const R* image, R* dirty, hipStream_t s);
+bool launch_fft(bool grid, const DevParams& P, const uint32_t* mask, const uint8_t* rows, cpx<R>* stack,
+                cpx<R>* inter, const cpx<R>* tw, const R* corr, const R* image, R* dirty, hipStream_t s);
 
 }  // namespace wsg

@@ -4,12 +4,11 @@
 // bin = k_bin_count, scan, k_bin_scatter, k_bin_local_sort (by touch class and
 //       support start), k_tile_occupancy
 // grid_visibilities:   bin -> k_grid_tiles (3-D scatter into the occupied tiles
-//                      of the stack [t][r][s]) -> k_grid_fft_a (IFFT along s,
-//                      crop, lines [t][r][q]) -> k_transpose ([t][q][r]) ->
-//                      k_grid_fft_b (IFFT along r, crop, w-screen, sum over
-//                      layers, correction) -> dirty [N][N]
+//                      of the stack) -> k_grid_fft_a (IFFT along s, crop,
+//                      lines [t][q][r]) -> k_grid_fft_b (IFFT along r, crop,
+//                      w-screen, sum over layers, correction) -> dirty [N][N]
 // degrid_visibilities: bin; k_degrid_fft_b (correction, w-screen, pad, FFT
-//                      along p, lines [t][q][r]) -> k_transpose ([t][r][q]) ->
+//                      along p, lines [t][q][r]) ->
 //                      k_degrid_fft_a (pad, FFT along q, occupied tiles) ->
 //                      k_degrid_tiles (3-D gather, one part per tile reached) ->
 //                      k_degrid_finish (sum of parts, phase, fold) -> vis [M]
@@ -140,7 +139,7 @@ struct wsg_plan {
 namespace {
 
 struct Layout {
-    size_t stack, inter, inter2, rec, rec2, part, count, start, cursor, bsums, cls, occ, rows, chan, tpos, tlist, skipped,
+    size_t stack, inter, rec, rec2, part, count, start, cursor, bsums, cls, occ, rows, mask, chan, tpos, tlist, skipped,
         total;
     int nch, nbins, nscan;
     int last_layer;    // end of the last channel's layers on the virtual layer axis
@@ -168,7 +167,7 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     L.nch = nch;
     L.last_layer = (nch - 1) * p->nbt * kTileT + p->pp.n_layers();
     L.pass_layers = std::min(L.last_layer, std::max(1, std::min(tiles_per_pass, nch * p->nbt)) * kTileT);
-    const size_t Np = size_t(p->pp.Nprime), N = size_t(p->pp.N), nl = size_t(L.pass_layers);
+    const size_t Np = size_t(p->pp.Nprime), nl = size_t(L.pass_layers);
     L.nbins = nch * p->nbins();
     L.nscan = (L.nbins + 1023) / 1024;
     // the skipped counter sits at offset 0 whatever M and the precision
@@ -181,6 +180,7 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     L.cls = off;     off += al256(size_t(L.nbins) * 8 * 4);
     L.occ = off;     off += al256(size_t(L.nbins));
     L.rows = off;    off += al256(size_t(nch) * p->nbt * p->nbr);
+    L.mask = off;    off += al256(size_t(nch) * p->nbt * p->nbr * mask_words(p->nbs) * 4);
     L.tpos = off;    off += al256(size_t(L.nbins + 1) * 4);
     L.tlist = off;   off += al256(size_t(L.nbins) * 4);
     L.chan = off;    off += al256(sizeof(long long) * (kMaxChannels + 1)) + al256(sizeof(int) * (kMaxChannels + 1));
@@ -188,8 +188,7 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     // strides then meet the memory channels the same way whatever precedes them)
     off = al2m(off);
     L.stack = off;   off += al2m(nl * Np * Np * cs);
-    L.inter = off;   off += al2m(nl * N * Np * cs);
-    L.inter2 = off;  off += al2m(nl * N * Np * cs);   // the transposed intermediate
+    L.inter = off;   off += al2m(nl * size_t(inter_blocks(p->pp.N)) * 16 * Np * cs);
     L.rec = off;     off += al256(size_t(M) * rs);
     L.rec2 = off;    off += al256(size_t(M) * rs);
     L.part = off;    off += al256(size_t(8) * size_t(M) * cs);   // degrid: per-tile parts
@@ -214,6 +213,7 @@ DevParams dev_params(const wsg_plan* p) {
     P.nch = 1;
     P.pl0 = 0;
     P.pln = p->pp.n_layers();
+    P.classes = pass_a_classes(p->pp.Nprime);
     P.umul = p->pp.l_max / p->pp.x0;
     P.nscale = p->pp.n_scale;
     P.zshift = p->pp.z_shift;
@@ -297,6 +297,7 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
     auto* cls = reinterpret_cast<uint32_t*>(w + L.cls);
     auto* occ = reinterpret_cast<uint8_t*>(w + L.occ);
     auto* rows = reinterpret_cast<uint8_t*>(w + L.rows);
+    auto* mask = reinterpret_cast<uint32_t*>(w + L.mask);
     auto* tpos = reinterpret_cast<uint32_t*>(w + L.tpos);
     auto* tlist = reinterpret_cast<uint32_t*>(w + L.tlist);
     auto* coff = reinterpret_cast<long long*>(w + L.chan);
@@ -333,10 +334,11 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
                                (const uint32_t*)start, cls, P);
         }
         fill<uint8_t>(rows, size_t(L.nch) * P.nbt * P.nbr, uint8_t(0), s);
+        fill<uint32_t>(mask, size_t(L.nch) * P.nbt * P.nbr * mask_words(P.nbs), 0u, s);
         // occupancy marks, then the ordered list of occupied tiles (the bin
         // counts are no longer needed: they take the 32-bit marks for the scan)
         hipLaunchKernelGGL(k_tile_occupancy, dim3((L.nbins + 255) / 256), dim3(256), 0, s, (const uint32_t*)start,
-                           (const uint32_t*)cls, P, occ, rows, count);
+                           (const uint32_t*)cls, P, occ, rows, mask, count);
         scan(count, tpos, bsums, L.nbins, s);
         hipLaunchKernelGGL(k_tile_list, dim3((L.nbins + 255) / 256), dim3(256), 0, s, (const uint8_t*)occ,
                            (const uint32_t*)tpos, L.nbins, tlist);
@@ -354,11 +356,10 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
     char* w = static_cast<char*>(ws);
     auto* stack = reinterpret_cast<cpx<R>*>(w + L.stack);
     auto* inter = reinterpret_cast<cpx<R>*>(w + L.inter);
-    auto* inter2 = reinterpret_cast<cpx<R>*>(w + L.inter2);
     auto* start = reinterpret_cast<uint32_t*>(w + L.start);
     auto* cls = reinterpret_cast<uint32_t*>(w + L.cls);
-    auto* occ = reinterpret_cast<uint8_t*>(w + L.occ);
     auto* rows = reinterpret_cast<uint8_t*>(w + L.rows);
+    auto* mask = reinterpret_cast<uint32_t*>(w + L.mask);
     auto* tpos = reinterpret_cast<uint32_t*>(w + L.tpos);
     auto* tlist = reinterpret_cast<uint32_t*>(w + L.tlist);
     const bool f64 = sizeof(R) == 8;
@@ -386,11 +387,9 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
                 launch_tiles<R>(true, P.W, P.Wz, plan->same_design, nblocks, rec, start, cls, tlist, tpos, Q, coef,
                                 coefz, prep_vis, stack, nullptr, 0, s);
             }
-            launch_fft<R>(true, Q, occ, rows, stack, inter, inter2, tw, corr, nullptr,
-                          static_cast<R*>(out), s);
+            launch_fft<R>(true, Q, mask, rows, stack, inter, tw, corr, nullptr, static_cast<R*>(out), s);
         } else {
-            launch_fft<R>(false, Q, occ, rows, stack, inter, inter2, tw, corr,
-                          static_cast<const R*>(in), nullptr, s);
+            launch_fft<R>(false, Q, mask, rows, stack, inter, tw, corr, static_cast<const R*>(in), nullptr, s);
             if (M > 0) {
                 StageMark mark(s, 7);
                 launch_tiles<R>(false, P.W, P.Wz, plan->same_design, nblocks, rec, start, cls, tlist, tpos, Q, coef,
@@ -466,6 +465,17 @@ int build_tables(wsg_plan* p) {
         tw64[k] = {std::cos(a), std::sin(a)};
         tw32[k] = {float(tw64[k].x), float(tw64[k].y)};
     }
+    // pass A's twiddles behind them (pass_a_table)
+    const PassATable ta = pass_a_table(Np);
+    auto add = [&](int k, int n) {           // exp(i 2 pi k / n), n a divisor of Np
+        const int i = int((long long)k * (Np / n) % Np);
+        tw64.push_back(tw64[i]);
+        tw32.push_back(tw32[i]);
+    };
+    for (int i = 0; i < ta.second; ++i) add((i / 16) * (i % 16), 256);
+    for (int i = 0; i < ta.last_radix * ta.last_n; ++i) add((i / ta.last_n) * (i % ta.last_n), ta.F);
+    for (int b = 0; b < Np / ta.F; ++b)
+        for (int n = 0; n < ta.F; ++n) add(b * n, Np);
     if ((rc = upload(&p->tw64, tw64.data(), tw64.size()))) return rc;
     if ((rc = upload(&p->tw32, tw32.data(), tw32.size()))) return rc;
 
