@@ -372,9 +372,8 @@ __global__ void __launch_bounds__(kAggThreads) k_bin_scatter(const double* __res
 // whose class contains m.  Classes are stored in Gray-code order (position q
 // holds class q ^ (q >> 1)): the records a tile needs from one bin are then at
 // most two contiguous ranges, ten over the eight bins.  Inside a class, records
-// are ordered by (layer, u, v) of their first support index, so that records
-// with the same support box are adjacent (long runs along Earth-rotation
-// tracks).
+// are ordered by their first support index, so that records with the same or a
+// near support box are adjacent (long runs along Earth-rotation tracks).
 // With separate widths, the layer axis uses Bt = 17 - W_z and the u, v axes
 // Buv = 17 - W.
 __device__ __forceinline__ int class_part(int hi, int B) { return hi ? kTileT - B : B; }
@@ -392,10 +391,20 @@ __device__ __forceinline__ int class_base(int q, int Bt, int Buv) {
     return b;
 }
 
+// Windows.  The tile kernels of width W <= 8 work on windows of kWin = 8 cells
+// along each axis, which hold the support of every record whose start lies in
+// the window's first 9 - W cells: a class's part of an axis is cut into blocks
+// of window_edge starts, and a class's records are ordered by block (layer, u,
+// v), then by start.  W > 8: blocks of one start.
+constexpr int kWin = 8;
+__host__ __device__ constexpr int window_edge(int W) { return W <= kWin ? kWin + 1 - W : 1; }
+// first start of the block of start i (of its class's part), and its size
+__device__ __forceinline__ int block_start(int i, int edge) { return i / edge * edge; }
+
 // One block per bin: LDS histogram over the 4096 in-tile positions enumerated
-// in (class position, layer, u, v) order, exclusive scan, scatter to `out`
-// (order among equal keys is arbitrary).  cls[8 bin + q] receives the start of
-// class position q in `out`.
+// in (class position, window block, start) order, exclusive scan, scatter to
+// `out` (order among equal keys is arbitrary).  cls[8 bin + q] receives the
+// start of class position q in `out`.
 template <typename R>
 __global__ void __launch_bounds__(256) k_bin_local_sort(const Rec<R>* __restrict__ in, Rec<R>* __restrict__ out,
                                                         const uint32_t* __restrict__ start,
@@ -404,6 +413,7 @@ __global__ void __launch_bounds__(256) k_bin_local_sort(const Rec<R>* __restrict
     __shared__ uint32_t hist[NK];
     __shared__ uint32_t sh[16];
     __shared__ int cbase[9];
+    __shared__ int blk[2][16];       // start l of the layer and the u, v axes: its block's start, size << 8, offset << 16
     const int bin = blockIdx.x;
     const uint32_t b0 = start[bin], b1 = start[bin + 1];
     if (b1 == b0) return;
@@ -411,14 +421,24 @@ __global__ void __launch_bounds__(256) k_bin_local_sort(const Rec<R>* __restrict
     const int tid = threadIdx.x;
     const int Buv = 17 - P.W, Bt = 17 - P.Wz;
     if (tid < 9) cbase[tid] = class_base(tid, Bt, Buv);
+    if (tid >= 32 && tid < 64) {
+        const int ax = (tid >> 4) & 1, l = tid & 15, B = ax ? Buv : Bt;
+        const int edge = P.W <= kWin ? window_edge(ax ? P.W : P.Wz) : 1;
+        const int hi = l >= B, i = hi ? l - B : l, b = block_start(i, edge);
+        blk[ax][l] = b | min(edge, class_part(hi, B) - b) << 8 | (i - b) << 16;
+    }
     for (int i = tid; i < NK; i += 256) hist[i] = 0u;
     __syncthreads();
     auto key_of = [&](const Rec<R>& r) {
         const int lr = int(r.ruv & 0xffffu) - br * kTileR, ls = int(r.ruv >> 16) - bs * kTileS;
         const int lt = int(r.rt) - bt * kTileT;
         const int c = class_of(lt, lr, ls, Bt, Buv);
-        const int it = (c & 1) ? lt - Bt : lt, ir = (c & 2) ? lr - Buv : lr, is = (c & 4) ? ls - Buv : ls;
-        return cbase[class_position(c)] + (it * class_part(c & 2, Buv) + ir) * class_part(c & 4, Buv) + is;
+        const int t = blk[0][lt], u = blk[1][lr], v = blk[1][ls];
+        const int nt = (t >> 8) & 255, nu = (u >> 8) & 255, nv = (v >> 8) & 255;
+        const int pu = class_part(c & 2, Buv), pv = class_part(c & 4, Buv);
+        // positions of the blocks before, then inside the block
+        return cbase[class_position(c)] + ((t & 255) * pu + nt * (u & 255)) * pv + nt * nu * (v & 255) +
+               ((t >> 16) * nu + (u >> 16)) * nv + (v >> 16);
     };
     for (uint32_t i = b0 + tid; i < b1; i += 256) atomicAdd(&hist[key_of(in[i])], 1u);
     __syncthreads();
@@ -630,7 +650,8 @@ __device__ __forceinline__ double bits_to_word(int v, double) { return __hiloint
 __device__ __forceinline__ int word_bits(float v) { return __float_as_int(v); }
 __device__ __forceinline__ int word_bits(double v) { return __double2loint(v); }
 
-// Scatter: residue classes (Romein 2012, extended to three axes).  Lane (x, y)
+// Scatter for W > 8, where a window of 8 cells does not hold the support:
+// residue classes (Romein 2012, extended to three axes).  Lane (x, y)
 // owns, among the W x W x WZ support cells of a record, the WZ cells whose u
 // and v indices are congruent to x and y modulo W, one per layer residue a: for
 // support start (dr, ds, dt) the u-cell dr + ((x - dr) mod W), the v-cell
@@ -931,6 +952,246 @@ __global__ void __launch_bounds__((ScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles
     for (int i = tid; i < nt_valid * kTileR * kTileS; i += NT) {
         const int ss = i % kTileS, rr = (i / kTileS) % kTileR, tt = i / (kTileR * kTileS);
         stack[tile_base(P, t0 - P.pl0 + tt, br, bs) * (kTileR * kTileS) + rr * kTileS + ss] = cpx<R>{tre[i], tim[i]};
+    }
+}
+
+// Matrix products of the tile kernels: D (16 x 16) += A (16 x 4) B (4 x 16),
+// lane l holding A[l % 16][l / 16], B[l / 16][l % 16] and, in element v, row
+// mfma_row(v) of column l % 16 of D.
+typedef float mfma_f4 __attribute__((ext_vector_type(4)));
+typedef double mfma_d4 __attribute__((ext_vector_type(4)));
+template <typename R>
+struct Mfma;
+template <>
+struct Mfma<float> {
+    using V = mfma_f4;
+    static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
+    static __device__ __forceinline__ V mul(float a, float b, V c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
+template <>
+struct Mfma<double> {
+    using V = mfma_d4;
+    static __device__ __forceinline__ int row(int lane, int v) { return (lane >> 4) + 4 * v; }
+    static __device__ __forceinline__ V mul(double a, double b, V c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
+
+// Scatter for W <= 8: over the records of one window the sums
+//     cell (x, y, a) += sum_k [wu_k(x) wv_k(y)] [wt_k(a) V_k]
+// are a product of a 64 x K matrix (rows the window's 8 x 8 pairs (x, y)) with a
+// K x 16 one (columns the 8 layers a times real and imaginary), four 16 x 16 x 4
+// matrix instructions per four records, summed in FP32 (FP64) as the vector
+// instructions were.  A wave stages 8 records at a time, lane (record, h)
+// evaluating segment h of the three kernel functions; each lands at its place of
+// the window (the places off the support are zero).  The sums stay in the
+// accumulators while the window does and are then added to the LDS tile, which
+// holds doubles for both precisions: ds_add_f32 takes 3 clocks per active lane
+// (192 for a full wave), ds_add_f64 8 for the wave.  On Earth-rotation tracks a
+// window holds 28 visits at wide field (a start of one cell 14), so that 95 % of
+// the matrix rows k carry a record.  Measured against the kernel of residue
+// classes (k_grid_tiles), per call: wide field 2.12 -> 1.61 ms (FP32, shared
+// binning) and 1.87 -> 1.55 (FP64), four channels at 1024^2 1.91 -> 0.95, W = 4
+// 0.295 -> 0.249, W = 8 FP64 0.121 -> 0.085, 5,000 scattered visibilities
+// 35 -> 21 us.
+template <typename R, int W, int WZ>
+struct MatScatterCfg {
+    static constexpr int kWaves = sizeof(R) == 4 ? 8 : 4;        // two blocks per CU (80 KB of LDS)
+    static constexpr int kThreads = 64 * kWaves;
+    static constexpr int kBatch = 8;                             // records staged at a time
+    static constexpr int kLT = 2 * kTileR * kTileS + 2;          // doubles between layers (skews them over the banks)
+    static constexpr int kSlot = 48;                             // values between slots (8 wu, 8 wv, 16 b, padding)
+};
+
+// b of lane `from` (a value of the batch's record) for the lane's own record
+__device__ __forceinline__ int lane_read(int v, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, v); }
+__device__ __forceinline__ float lane_read(float v, int from) {
+    return __int_as_float(lane_read(__float_as_int(v), from));
+}
+__device__ __forceinline__ double lane_read(double v, int from) {
+    return __hiloint2double(lane_read(__double2hiint(v), from), lane_read(__double2loint(v), from));
+}
+
+template <typename R, int W, int WZ, bool SAME, bool PREP>
+__global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles_mat(const Rec<R>* __restrict__ rec,
+                                                    const uint32_t* __restrict__ start,
+                                                    const uint32_t* __restrict__ cls,
+                                                    const uint32_t* __restrict__ tlist,
+                                                    const uint32_t* __restrict__ tpos, DevParams P,
+                                                    const R* __restrict__ coef_g, const R* __restrict__ coefz_g,
+                                                    const cpx<R>* __restrict__ vis, cpx<R>* __restrict__ stack) {
+    using Cfg = MatScatterCfg<R, W, WZ>;
+    using M = Mfma<R>;
+    constexpr int D = KernelDegree<R>::value, NW = Cfg::kWaves, NT = Cfg::kThreads, WB = Cfg::kBatch, LT = Cfg::kLT;
+    constexpr int EUV = window_edge(W), ET = window_edge(WZ), BUV = 17 - W, BT = 17 - WZ;
+    static_assert(W <= kWin && WZ <= W && WB * 8 == 64, "a wave stages 8 records, 8 segments each");
+    __shared__ double cells[kTileT * LT];                      // [t][r][s] real, imaginary
+    __shared__ __align__(16) R stage[NW * WB * Cfg::kSlot];
+    __shared__ TileSegs sg;
+
+    const int tile = tile_of_block(P, tlist, tpos);
+    if (tile < 0) return;     // unoccupied tiles are left unwritten and read as zero
+    const int br = tile % P.nbr, bs = (tile / P.nbr) % P.nbs, bt = tile / (P.nbr * P.nbs);
+    const int r0 = br * kTileR, s0 = bs * kTileS, t0 = bt * kTileT;
+    const int nt_valid = min(kTileT, P.n_layers - t0 % (P.nbt * kTileT));   // layers of its channel
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < 64) tile_segments(start, cls, P, bt, bs, br, sg);
+    __syncthreads();
+    const int nseg = sg.n;
+    const uint32_t total = sg.off[nseg];
+    // this wave's part of the list
+    const uint32_t part = (total + NW - 1) / NW;
+    const uint32_t q0 = min(total, part * uint32_t(wv)), q1 = min(total, q0 + part);
+    // the lane's record of the next 64 (PREP: of the next two 64s, and the first one's value)
+    uint32_t vn = q0 + uint32_t(lane);
+    int g = 0;
+    Rec<R> nxt{}, nxt2{};
+    cpx<R> nval{R(0), R(0)};
+    if (vn < q1) nxt = rec[seg_advance(sg, nseg, vn, g)];
+    if constexpr (PREP) {
+        if (vn < q1) nval = vis[nxt.idx & 0x7fffffffu];
+        if (vn + 64 < q1) nxt2 = rec[seg_advance(sg, nseg, vn + 64, g)];
+    }
+    for (int i = tid; i < kTileT * LT; i += NT) cells[i] = 0.0;
+    R* st = stage + wv * (WB * Cfg::kSlot);
+    for (int i = lane; i < WB * Cfg::kSlot; i += 64) st[i] = R(0);
+    __syncthreads();
+
+    if (q1 > q0) {
+        // staging: lane (record lane % 8, segment h)
+        const int slot = lane & 7, h = lane >> 3;
+        R creg[D + 1], czreg[SAME ? 1 : D + 1];
+#pragma unroll
+        for (int k = 0; k <= D; ++k) {
+            creg[k] = coef_g[min(h, W - 1) * (D + 1) + k];
+            if constexpr (!SAME) czreg[k] = coefz_g[min(h, WZ - 1) * (D + 1) + k];
+        }
+        R* my = st + slot * Cfg::kSlot;
+        // operands: row i = 8 xb + y of block q is the pair (x, y), x = 2 q + xb
+        const int kk = lane >> 4;
+        const R* op = st + kk * Cfg::kSlot;
+        const int at_u = ((lane >> 3) & 1) * 4, at_v = 8 + (lane & 7), at_b = 16 + (lane & 15);
+        typename M::V acc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = typename M::V{R(0), R(0), R(0), R(0)};
+        int cur = -1;           // the window, packed
+        auto flush = [&]() {
+            const int wr = (cur & 255) - 128, ws = ((cur >> 8) & 255) - 128, wt = ((cur >> 16) & 255) - 128;
+            const int t = wt + ((lane & 15) >> 1);
+            const bool tok = unsigned(t) < unsigned(nt_valid);
+            double* base = cells + t * LT + (wr * kTileS + ws) * 2 + (lane & 1);
+            bool sok[4];
+            int off[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = M::row(lane, v), y = i & 7;
+                sok[v] = tok && unsigned(ws + y) < unsigned(kTileS);
+                off[v] = ((i >> 3) * kTileS + y) * 2;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = wr + 2 * q + (M::row(lane, v) >> 3);
+                    if (sok[v] && unsigned(r) < unsigned(kTileR)) atomicAdd(base + off[v] + q * (4 * kTileS), double(acc[q][v]));
+                }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = typename M::V{R(0), R(0), R(0), R(0)};
+        };
+        for (uint32_t base = q0; base < q1; base += 64) {
+            const int n = __builtin_amdgcn_readfirstlane(int(min(64u, q1 - base)));
+            // the lane's record: window, place in it, value
+            const int dr = wrap_offset(int(nxt.ruv & 0xffffu), r0, P.Np);
+            const int ds = wrap_offset(int(nxt.ruv >> 16), s0, P.Np);
+            const int dt = int(nxt.rt) - t0;
+            auto place = [](int d, int B, int edge) {
+                const int l = d & (kTileR - 1);
+                return (l >= B ? l - B : l) % edge;
+            };
+            const int ou = place(dr, BUV, EUV), ov = place(ds, BUV, EUV), ot = place(dt, BT, ET);
+            const int win = (dr - ou + 128) | ((ds - ov + 128) << 8) | ((dt - ot + 128) << 16);
+            const int places = ou | (ov << 4) | (ot << 8);
+            R nu0 = nxt.nu[0], nu1 = nxt.nu[1], nu2 = nxt.nu[2], v0 = nxt.v[0], v1 = nxt.v[1];
+            if constexpr (PREP) {
+                const double vx = double(nval.x), vy = (nxt.idx & 0x80000000u) ? -double(nval.y) : double(nval.y);
+                const double co = double(nxt.v[0]), sn = -double(nxt.v[1]);
+                v0 = R(vx * co - vy * sn);
+                v1 = R(vx * sn + vy * co);
+            }
+            if (lane >= n) nu0 = nu1 = nu2 = v0 = v1 = R(0);        // finite weights, no value
+            const int before = __shfl_up(win, 1, 64);
+            const uint64_t moved = __ballot(lane < n && win != (lane == 0 ? cur : before));
+            vn += 64;
+            if constexpr (PREP) {
+                nxt = nxt2;
+                if (vn < q1) nval = vis[nxt.idx & 0x7fffffffu];
+                if (vn + 64 < q1) nxt2 = rec[seg_advance(sg, nseg, vn + 64, g)];
+            } else {
+                if (vn < q1) nxt = rec[seg_advance(sg, nseg, vn, g)];
+            }
+            for (int b0 = 0; b0 < n; b0 += WB) {
+                {
+                    const int from = b0 + slot;
+                    const R a0 = lane_read(nu0, from), a1 = lane_read(nu1, from), a2 = lane_read(nu2, from);
+                    const R x = lane_read(v0, from), y = lane_read(v1, from);
+                    const int pl = lane_read(places, from);
+                    R hu = creg[D], hv = creg[D], ht = SAME ? creg[D] : czreg[D];
+#pragma unroll
+                    for (int k = D - 1; k >= 0; --k) {
+                        hu = hu * a0 + creg[k];
+                        hv = hv * a1 + creg[k];
+                        ht = ht * a2 + (SAME ? creg[k] : czreg[k]);
+                    }
+                    const int pu = ((pl & 15) + h) & 7, pv = (((pl >> 4) & 15) + h) & 7, pt = ((pl >> 8) + h) & 7;
+                    my[(pu & 1) * 4 + (pu >> 1)] = h < W ? hu : R(0);
+                    my[8 + pv] = h < W ? hv : R(0);
+                    my[16 + 2 * pt] = h < WZ ? x * ht : R(0);
+                    my[17 + 2 * pt] = h < WZ ? y * ht : R(0);
+                }
+                wave_sync();
+#pragma unroll
+                for (int g4 = 0; g4 < WB; g4 += 4) {
+                    const int first = b0 + g4;
+                    if (first >= n) break;
+                    const R* o = op + g4 * Cfg::kSlot;
+                    const R b = o[at_b], fv = o[at_v];
+                    R fu[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) fu[q] = o[at_u + q] * fv;
+                    const uint32_t m = uint32_t(moved >> first) & 15u;
+                    if (m == 0) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[q] = M::mul(fu[q], b, acc[q]);
+                        continue;
+                    }
+                    // the window moves inside the four: one product per window
+                    for (int lo = 0; lo < 4;) {
+                        if (m & (1u << lo)) {
+                            if (cur >= 0) flush();
+                            cur = __builtin_amdgcn_readlane(win, first + lo);
+                        }
+                        const uint32_t rest = m >> (lo + 1);
+                        const int hi = rest ? lo + 1 + __builtin_ctz(rest) : 4;
+                        const R bb = kk >= lo && kk < hi ? b : R(0);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[q] = M::mul(fu[q], bb, acc[q]);
+                        lo = hi;
+                    }
+                }
+                wave_sync();
+            }
+        }
+        flush();
+    }
+    __syncthreads();
+    // write the tile: rows of kTileS cells
+    for (int i = tid; i < nt_valid * kTileR * kTileS; i += NT) {
+        const int c = i % (kTileR * kTileS), tt = i / (kTileR * kTileS);
+        const double* at = cells + tt * LT + 2 * c;
+        stack[tile_base(P, t0 - P.pl0 + tt, br, bs) * (kTileR * kTileS) + c] = cpx<R>{R(at[0]), R(at[1])};
     }
 }
 

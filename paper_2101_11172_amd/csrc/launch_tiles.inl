@@ -20,13 +20,28 @@ template <typename R, int W, int WZ, bool SAME>
 void launch_tiles_w(bool grid, int nblocks, const Rec<R>* rec, const uint32_t* start, const uint32_t* cls,
                     const uint32_t* tlist, const uint32_t* tpos, const DevParams& P, const R* coef, const R* coefz,
                     const cpx<R>* vis, cpx<R>* stack, cpx<R>* part, size_t part_stride, hipStream_t s) {
-    if (grid && vis)
-        hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, true>), dim3(nblocks), dim3(ScatterCfg<R, W, WZ>::kThreads),
-                           0, s, rec, start, cls, tlist, tpos, P, coef, coefz, vis, stack);
-    else if (grid)
-        hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, false>), dim3(nblocks), dim3(ScatterCfg<R, W, WZ>::kThreads),
-                           0, s, rec, start, cls, tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
-    else
+    if (grid && W <= kWin) {
+        // the matrix kernel, wherever the window of 8 cells holds the support
+        if constexpr (W <= kWin) {
+            constexpr int TH = MatScatterCfg<R, W, WZ>::kThreads;
+            if (vis)
+                hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec, start,
+                                   cls, tlist, tpos, P, coef, coefz, vis, stack);
+            else
+                hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec, start,
+                                   cls, tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
+        }
+    } else if (grid) {
+        if constexpr (W > kWin) {
+            constexpr int TH = ScatterCfg<R, W, WZ>::kThreads;
+            if (vis)
+                hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec, start, cls,
+                                   tlist, tpos, P, coef, coefz, vis, stack);
+            else
+                hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec, start, cls,
+                                   tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
+        }
+    } else
         hipLaunchKernelGGL((k_degrid_tiles<R, W, WZ, SAME>), dim3(nblocks), dim3(256), 0, s, rec, start, cls, tlist,
                            tpos, P, coef, coefz, (const cpx<R>*)stack, part, part_stride);
 }
