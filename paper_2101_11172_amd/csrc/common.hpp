@@ -157,6 +157,18 @@ __device__ __forceinline__ size_t tile_base(const DevParams& P, int tl, int br, 
     return (size_t(tl) * P.nbr + br) * P.nbs + bs;
 }
 
+// One marked tile: its index and the records that reach it, at most ten ranges of
+// the record array concatenated into a virtual list [0, total): range g holds
+// the virtual positions from off[g] (0xffffffff past the last), position v the
+// record v + delta[g]; bits 3 g .. 3 g + 2 of nbrs are the range's bin, the set
+// it | ir << 1 | is << 2 of axes along which it lies one tile back.
+struct __align__(128) TileRec {
+    uint32_t tile, total, nbrs, pad;
+    uint32_t off[10];
+    uint32_t delta[10];
+    uint32_t pad2[8];
+};
+
 // blockIdx -> logical block so that each XCD (blocks are dealt round-robin to
 // the 8 XCDs) walks a contiguous range of logical blocks.  For uniform work
 // (the FFT passes): neighbouring lines share cache lines in that XCD's L2.

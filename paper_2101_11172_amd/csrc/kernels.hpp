@@ -506,12 +506,50 @@ static __global__ void k_tile_occupancy(const uint32_t* __restrict__ start, cons
     }
 }
 
-// The occupied tiles in tile order: list[pos[t]] = t for every marked tile t,
-// pos the exclusive scan of the flags (pos[n] = number of marked tiles).
-static __global__ void k_tile_list(const uint8_t* __restrict__ occ, const uint32_t* __restrict__ pos, int n,
-                            uint32_t* __restrict__ list) {
+// The marked tiles in tile order: list[pos[t]] for every marked tile t, pos the
+// exclusive scan of the flags (pos[n] = number of marked tiles).  A tile's ranges
+// are gathered here, once for both directions, so that a tile block needs one
+// load before its records.
+static __global__ void k_tile_list(const uint8_t* __restrict__ occ, const uint32_t* __restrict__ pos,
+                            const uint32_t* __restrict__ start, const uint32_t* __restrict__ cls, DevParams P,
+                            TileRec* __restrict__ list) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n && occ[t]) list[pos[t]] = uint32_t(t);
+    if (t >= P.nch * P.nbt * P.nbs * P.nbr || !occ[t]) return;
+    const int br = t % P.nbr, bs = (t / P.nbr) % P.nbs, bt = t / (P.nbr * P.nbs);
+    TileRec& T = list[pos[t]];
+    uint32_t total = 0, nbrs = 0;
+    int n = 0;
+    for (int nb = 0; nb < 8; ++nb) {
+        const int it = (nb >> 2) & 1, is = (nb >> 1) & 1, ir = nb & 1;
+        if (bt % P.nbt - it < 0) continue;      // not across a channel start
+        const int bin = ((bt - it) * P.nbs + (bs - is + P.nbs) % P.nbs) * P.nbr + (br - ir + P.nbr) % P.nbr;
+        const uint32_t b0 = start[bin], b1 = start[bin + 1];
+        if (b1 == b0) continue;
+        const int m = it | (ir << 1) | (is << 2);
+        uint32_t at[9];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) at[q] = cls[8 * size_t(bin) + q];
+        at[8] = b1;
+        uint32_t lo = 0;
+        bool in = false;
+#pragma unroll
+        for (int q = 0; q <= 8; ++q) {          // at most two runs of classes that contain m
+            const bool need = q < 8 && ((q ^ (q >> 1)) & m) == m;
+            if (need && !in) lo = at[q];
+            if (!need && in && at[q] > lo) {
+                T.off[n] = total;
+                T.delta[n] = lo - total;
+                nbrs |= uint32_t(m) << (3 * n);
+                total += at[q] - lo;
+                ++n;
+            }
+            in = need;
+        }
+    }
+    T.tile = uint32_t(t);
+    T.total = total;
+    T.nbrs = nbrs;
+    for (; n < 10; ++n) T.off[n] = 0xffffffffu;
 }
 
 // ------------------------------------------------ 3-D scatter / gather tiles --
@@ -531,64 +569,22 @@ struct KernelDegree {
     static constexpr int value = sizeof(R) == 8 ? 16 : 8;
 };
 
-// The records that reach one tile: ranges [lo[g], lo[g] + off[g+1] - off[g])
-// of the record array, concatenated into a virtual list [0, off[n]).
-struct TileSegs {
-    uint32_t lo[64];
-    uint32_t off[65];
-    uint8_t nbr[64];      // neighbour set of the range's bin: it | ir << 1 | is << 2
-    int n;
-};
-
-// Built by wave 0 (a block barrier must follow).  Lane l handles class position
-// q = l & 7 of the bin one tile back along t, v, u by the bits of l >> 3.
-__device__ __forceinline__ void tile_segments(const uint32_t* __restrict__ start, const uint32_t* __restrict__ cls,
-                                              const DevParams& P, int bt, int bs, int br, TileSegs& sg) {
-    const int lane = threadIdx.x & 63;
-    const int nb = lane >> 3, q = lane & 7;
-    const int it = (nb >> 2) & 1, is = (nb >> 1) & 1, ir = nb & 1;
-    uint32_t lo = 0, hi = 0;
-    bool need = false;
-    if (bt % P.nbt - it >= 0) {      // not across a channel start
-        const int bin = ((bt - it) * P.nbs + (bs - is + P.nbs) % P.nbs) * P.nbr + (br - ir + P.nbr) % P.nbr;
-        const uint32_t b0 = start[bin], b1 = start[bin + 1];
-        if (b1 > b0) {
-            lo = cls[8 * size_t(bin) + q];
-            hi = q < 7 ? cls[8 * size_t(bin) + q + 1] : b1;
-            const int c = q ^ (q >> 1);
-            const int m = it | (ir << 1) | (is << 2);
-            need = (c & m) == m;
-        }
-    }
-    const uint32_t len = need ? hi - lo : 0u;
-    const unsigned long long nm = __ballot(need);
-    const bool first = need && !(q > 0 && ((nm >> (lane - 1)) & 1ull));
-    const unsigned long long fm = __ballot(first);
-    uint32_t inc = len;
+// Record array index of virtual position v of the tile's list; m: its bin's set
+// of axes.  T is wave-uniform, so the ranges come from scalar registers.
+__device__ __forceinline__ uint32_t tile_record(const TileRec& T, uint32_t v, uint32_t& m) {
+    uint32_t d = T.delta[0], k = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
+    for (int g = 1; g < 10; ++g) {
+        const bool past = v >= T.off[g];
+        d = past ? T.delta[g] : d;
+        k = past ? 3 * g : k;
     }
-    if (first) {
-        const int g = __popcll(fm & ((1ull << lane) - 1ull));
-        sg.lo[g] = lo;
-        sg.off[g] = inc - len;
-        sg.nbr[g] = uint8_t(it | (ir << 1) | (is << 2));
-    }
-    if (lane == 63) {
-        const int n = __popcll(fm);
-        sg.n = n;
-        sg.off[n] = inc;
-    }
+    m = (T.nbrs >> k) & 7u;
+    return v + d;
 }
-
-// Record array index of virtual position v; g is the caller's current range,
-// moved forward to the one holding v (a lane's positions only grow, so the
-// search is incremental).
-__device__ __forceinline__ uint32_t seg_advance(const TileSegs& sg, int n, uint32_t v, int& g) {
-    while (g + 1 < n && sg.off[g + 1] <= v) ++g;
-    return sg.lo[g] + (v - sg.off[g]);
+__device__ __forceinline__ uint32_t tile_record(const TileRec& T, uint32_t v) {
+    uint32_t m;
+    return tile_record(T, v, m);
 }
 
 // Signed offset of a support start from the tile origin along a periodic axis.
@@ -607,16 +603,15 @@ __device__ __forceinline__ int mod_w(int x) {
 
 // The launch has one block per tile of the current layer pass (tile layers
 // pl0 / kTileT onwards), and the blocks take the pass's occupied tiles from the
-// ordered list (groups of 4 neighbours per XCD); the result is the global tile
-// index, or -1 for a block beyond the occupied tiles (it exits at once).
-__device__ __forceinline__ int tile_of_block(const DevParams& P, const uint32_t* __restrict__ tlist,
-                                             const uint32_t* __restrict__ tpos) {
+// ordered list (groups of 4 neighbours per XCD); the result is the place in the
+// list, or -1 for a block beyond the occupied tiles (it exits at once).
+__device__ __forceinline__ int tile_of_block(const DevParams& P, const uint32_t* __restrict__ tpos) {
     const int per_layer = P.nbs * P.nbr;
     const int nbt_pass = (P.pln + kTileT - 1) / kTileT;
     const int a = (P.pl0 / kTileT) * per_layer, e = a + nbt_pass * per_layer;
     const int first = int(tpos[a]), cnt = int(tpos[e]) - first;
     if (int(blockIdx.x) >= cnt) return -1;
-    return int(tlist[first + xcd_interleave<4>(blockIdx.x, cnt)]);
+    return first + xcd_interleave<4>(blockIdx.x, cnt);
 }
 
 // Kernel weights of one record on the three axes by Horner's rule: u and v
@@ -699,9 +694,7 @@ struct __align__(16) ScatterStage {
 // issued a round before its staging.
 template <typename R, int W, int WZ, bool SAME, bool PREP>
 __global__ void __launch_bounds__((ScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles(const Rec<R>* __restrict__ rec,
-                                                    const uint32_t* __restrict__ start,
-                                                    const uint32_t* __restrict__ cls,
-                                                    const uint32_t* __restrict__ tlist,
+                                                    const TileRec* __restrict__ tlist,
                                                     const uint32_t* __restrict__ tpos, DevParams P,
                                                     const R* __restrict__ coef_g, const R* __restrict__ coefz_g,
                                                     const cpx<R>* __restrict__ vis, cpx<R>* __restrict__ stack) {
@@ -710,10 +703,11 @@ __global__ void __launch_bounds__((ScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles
     __shared__ R tre[Cfg::kCells];
     __shared__ R tim[Cfg::kCells];
     __shared__ ScatterStage<R, W, WZ> st;
-    __shared__ TileSegs sg;
 
-    const int tile = tile_of_block(P, tlist, tpos);
-    if (tile < 0) return;     // unoccupied tiles are left unwritten and read as zero
+    const int place = tile_of_block(P, tpos);
+    if (place < 0) return;     // unoccupied tiles are left unwritten and read as zero
+    const TileRec& T = tlist[place];
+    const int tile = int(T.tile);
     const int br = tile % P.nbr, bs = (tile / P.nbr) % P.nbs, bt = tile / (P.nbr * P.nbs);
     const int r0 = br * kTileR, s0 = bs * kTileS, t0 = bt * kTileT;
     const int nt_valid = min(kTileT, P.n_layers - t0 % (P.nbt * kTileT));   // layers of its channel
@@ -721,11 +715,9 @@ __global__ void __launch_bounds__((ScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     constexpr int NT = Cfg::kThreads, NW = Cfg::kWaves;
-    if (tid < 64) tile_segments(start, cls, P, bt, bs, br, sg);
     for (int i = tid; i < Cfg::kCells; i += NT) tre[i] = tim[i] = R(0);
     __syncthreads();
-    const int nseg = sg.n;
-    const uint32_t total = sg.off[nseg];
+    const uint32_t total = T.total;
     // this wave's part of the list
     const uint32_t part = (total + NW - 1) / NW;
     const uint32_t q0 = min(total, part * uint32_t(wv)), q1 = min(total, q0 + part);
@@ -823,16 +815,14 @@ __global__ void __launch_bounds__((ScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles
                 }
             }
         }
-        // the lane's next record: virtual position vn in range g (ranges only
-        // move forward as vn grows by WB per round)
+        // the lane's next record: virtual position vn
         uint32_t vn = q0 + uint32_t(rl);
-        int g = 0;
         Rec<R> nxt{}, nxt2{};
         cpx<R> nval{R(0), R(0)};
-        if (vn < q1) nxt = rec[seg_advance(sg, nseg, vn, g)];
+        if (vn < q1) nxt = rec[tile_record(T, vn)];
         if constexpr (PREP) {
             if (vn < q1) nval = vis[nxt.idx & 0x7fffffffu];
-            if (vn + WB < q1) nxt2 = rec[seg_advance(sg, nseg, vn + WB, g)];
+            if (vn + WB < q1) nxt2 = rec[tile_record(T, vn + WB)];
         }
         for (uint32_t base = q0; base < q1; base += WB) {
             const int n = __builtin_amdgcn_readfirstlane(int(min(uint32_t(WB), q1 - base)));
@@ -897,9 +887,9 @@ __global__ void __launch_bounds__((ScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles
             if constexpr (PREP) {
                 nxt = nxt2;
                 if (vn < q1) nval = vis[nxt.idx & 0x7fffffffu];
-                if (vn + WB < q1) nxt2 = rec[seg_advance(sg, nseg, vn + WB, g)];
+                if (vn + WB < q1) nxt2 = rec[tile_record(T, vn + WB)];
             } else {
-                if (vn < q1) nxt = rec[seg_advance(sg, nseg, vn, g)];
+                if (vn < q1) nxt = rec[tile_record(T, vn)];
             }
 
             // groups of four slots with fixed offsets (one address update per
@@ -1014,11 +1004,34 @@ __device__ __forceinline__ double lane_read(double v, int from) {
     return __hiloint2double(lane_read(__double2hiint(v), from), lane_read(__double2loint(v), from));
 }
 
+// Tiles a block of a matrix kernel takes one after the other: a block's start (its
+// arguments, the list, the first records: four loads that wait for each other)
+// took a quarter of its time, so a launch of many tiles gives each block several,
+// a stride of the launch apart (neighbours, which differ little in work, then go
+// to different blocks), the next one's records loaded during the current one.
+// Below two rounds of resident blocks each block keeps one tile.  With the ranges
+// from k_tile_list, wide field: FP32 scatter 1.61 -> 1.47 ms, FP64 1.55 -> 1.37;
+// four channels at 1024^2 0.95 -> 0.86; three passes at 4096^2 8.43 -> 7.66.  The
+// rest is issue: 18 vector and 13 scalar instructions per visit and a quarter of
+// the time in the matrix units.
+constexpr int kMostTiles = 16;
+struct TileRun {
+    int place, step, end;      // places of the list: place, place + step, ... < end
+};
+__device__ __forceinline__ bool tiles_of_block(const DevParams& P, const uint32_t* __restrict__ tpos, int resident,
+                                               TileRun& run) {
+    const int per_layer = P.nbs * P.nbr, a = (P.pl0 / kTileT) * per_layer;
+    const int first = int(tpos[a]), cnt = int(tpos[a + (P.pln + kTileT - 1) / kTileT * per_layer]) - first;
+    const int each = min(kMostTiles, max(1, cnt / (2 * resident)));
+    run.step = (cnt + each - 1) / each;
+    run.place = first + xcd_interleave<4>(blockIdx.x, run.step);
+    run.end = first + cnt;
+    return int(blockIdx.x) < run.step;
+}
+
 template <typename R, int W, int WZ, bool SAME, bool PREP>
 __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_tiles_mat(const Rec<R>* __restrict__ rec,
-                                                    const uint32_t* __restrict__ start,
-                                                    const uint32_t* __restrict__ cls,
-                                                    const uint32_t* __restrict__ tlist,
+                                                    const TileRec* __restrict__ tlist,
                                                     const uint32_t* __restrict__ tpos, DevParams P,
                                                     const R* __restrict__ coef_g, const R* __restrict__ coefz_g,
                                                     const cpx<R>* __restrict__ vis, cpx<R>* __restrict__ stack) {
@@ -1027,80 +1040,96 @@ __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_ti
     constexpr int D = KernelDegree<R>::value, NW = Cfg::kWaves, NT = Cfg::kThreads, WB = Cfg::kBatch, LT = Cfg::kLT;
     constexpr int EUV = window_edge(W), ET = window_edge(WZ), BUV = 17 - W, BT = 17 - WZ;
     static_assert(W <= kWin && WZ <= W && WB * 8 == 64, "a wave stages 8 records, 8 segments each");
-    __shared__ double cells[kTileT * LT];                      // [t][r][s] real, imaginary
+    __shared__ __align__(16) double cells[kTileT * LT];        // [t][r][s] real, imaginary
     __shared__ __align__(16) R stage[NW * WB * Cfg::kSlot];
-    __shared__ TileSegs sg;
 
-    const int tile = tile_of_block(P, tlist, tpos);
-    if (tile < 0) return;     // unoccupied tiles are left unwritten and read as zero
-    const int br = tile % P.nbr, bs = (tile / P.nbr) % P.nbs, bt = tile / (P.nbr * P.nbs);
-    const int r0 = br * kTileR, s0 = bs * kTileS, t0 = bt * kTileT;
-    const int nt_valid = min(kTileT, P.n_layers - t0 % (P.nbt * kTileT));   // layers of its channel
+    TileRun run;
+    if (!tiles_of_block(P, tpos, 512, run)) return;     // unoccupied tiles are left unwritten and read as zero
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid < 64) tile_segments(start, cls, P, bt, bs, br, sg);
-    __syncthreads();
-    const int nseg = sg.n;
-    const uint32_t total = sg.off[nseg];
-    // this wave's part of the list
-    const uint32_t part = (total + NW - 1) / NW;
-    const uint32_t q0 = min(total, part * uint32_t(wv)), q1 = min(total, q0 + part);
-    // the lane's record of the next 64 (PREP: of the next two 64s, and the first one's value)
-    uint32_t vn = q0 + uint32_t(lane);
-    int g = 0;
-    Rec<R> nxt{}, nxt2{};
-    cpx<R> nval{R(0), R(0)};
-    if (vn < q1) nxt = rec[seg_advance(sg, nseg, vn, g)];
-    if constexpr (PREP) {
-        if (vn < q1) nval = vis[nxt.idx & 0x7fffffffu];
-        if (vn + 64 < q1) nxt2 = rec[seg_advance(sg, nseg, vn + 64, g)];
+    // this wave's part of a tile's list: [q0, q1)
+    auto part_of = [&](uint32_t total, uint32_t& q0, uint32_t& q1) {
+        const uint32_t part = (total + NW - 1) / NW;
+        q0 = min(total, part * uint32_t(wv));
+        q1 = min(total, q0 + part);
+    };
+    // staging: lane (record lane % 8, segment h); segments past the width are zero
+    const int slot = lane & 7, h = lane >> 3;
+    R creg[D + 1], czreg[SAME ? 1 : D + 1];
+#pragma unroll
+    for (int k = 0; k <= D; ++k) {
+        creg[k] = h < W ? coef_g[h * (D + 1) + k] : R(0);
+        if constexpr (!SAME) czreg[k] = h < WZ ? coefz_g[h * (D + 1) + k] : R(0);
     }
+    uint32_t q0, q1;
+    part_of(tlist[run.place].total, q0, q1);
+    Rec<R> nxt{};              // the lane's record of the next 64, and (PREP) its value
+    cpx<R> nval{R(0), R(0)};
+    if (q0 + uint32_t(lane) < q1) nxt = rec[tile_record(tlist[run.place], q0 + uint32_t(lane))];
     for (int i = tid; i < kTileT * LT; i += NT) cells[i] = 0.0;
     R* st = stage + wv * (WB * Cfg::kSlot);
     for (int i = lane; i < WB * Cfg::kSlot; i += 64) st[i] = R(0);
+    if constexpr (PREP) {
+        if (q0 + uint32_t(lane) < q1) nval = vis[nxt.idx & 0x7fffffffu];
+    }
+    R* my = st + slot * Cfg::kSlot;
+    // operands: row i = 8 xb + y of block q is the pair (x, y), x = 4 xb + q
+    const int kk = lane >> 4;
+    const R* op = st + kk * Cfg::kSlot;
+    const int at_u = ((lane >> 3) & 1) * 4, at_v = 8 + (lane & 7), at_b = 16 + (lane & 15);
+    typename M::V acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = typename M::V{R(0), R(0), R(0), R(0)};
     __syncthreads();
 
-    if (q1 > q0) {
-        // staging: lane (record lane % 8, segment h)
-        const int slot = lane & 7, h = lane >> 3;
-        R creg[D + 1], czreg[SAME ? 1 : D + 1];
-#pragma unroll
-        for (int k = 0; k <= D; ++k) {
-            creg[k] = coef_g[min(h, W - 1) * (D + 1) + k];
-            if constexpr (!SAME) czreg[k] = coefz_g[min(h, WZ - 1) * (D + 1) + k];
-        }
-        R* my = st + slot * Cfg::kSlot;
-        // operands: row i = 8 xb + y of block q is the pair (x, y), x = 2 q + xb
-        const int kk = lane >> 4;
-        const R* op = st + kk * Cfg::kSlot;
-        const int at_u = ((lane >> 3) & 1) * 4, at_v = 8 + (lane & 7), at_b = 16 + (lane & 15);
-        typename M::V acc[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = typename M::V{R(0), R(0), R(0), R(0)};
+    for (;;) {
+        const TileRec& T = tlist[run.place];
+        const int tile = int(T.tile);
+        const int br = tile % P.nbr, bs = (tile / P.nbr) % P.nbs, bt = tile / (P.nbr * P.nbs);
+        const int r0 = br * kTileR, s0 = bs * kTileS, t0 = bt * kTileT;
+        const int nt_valid = min(kTileT, P.n_layers - t0 % (P.nbt * kTileT));   // layers of its channel
+        const bool more = run.place + run.step < run.end;
+        const TileRec& T2 = tlist[more ? run.place + run.step : run.place];
+        uint32_t n0 = 0, n1 = 0;
+        if (more) part_of(T2.total, n0, n1);
         int cur = -1;           // the window, packed
         auto flush = [&]() {
             const int wr = (cur & 255) - 128, ws = ((cur >> 8) & 255) - 128, wt = ((cur >> 16) & 255) - 128;
             const int t = wt + ((lane & 15) >> 1);
-            const bool tok = unsigned(t) < unsigned(nt_valid);
-            double* base = cells + t * LT + (wr * kTileS + ws) * 2 + (lane & 1);
-            bool sok[4];
-            int off[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = M::row(lane, v), y = i & 7;
-                sok[v] = tok && unsigned(ws + y) < unsigned(kTileS);
-                off[v] = ((i >> 3) * kTileS + y) * 2;
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
+            if (unsigned(t) < unsigned(nt_valid)) {
+                // the cells outside the tile go to the padding behind the layer, without a branch per cell
+                double* base = cells + t * LT + (lane & 1);
+                const int c0 = wr * kTileS + ws;
+                bool sok[4];
+                int off[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int r = wr + 2 * q + (M::row(lane, v) >> 3);
-                    if (sok[v] && unsigned(r) < unsigned(kTileR)) atomicAdd(base + off[v] + q * (4 * kTileS), double(acc[q][v]));
+                    const int i = M::row(lane, v), y = i & 7;
+                    sok[v] = unsigned(ws + y) < unsigned(kTileS);
+                    off[v] = c0 + (i >> 3) * 4 * kTileS + y;
                 }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int r = wr + 4 * (M::row(lane, v) >> 3) + q;
+                        const int c = sok[v] && unsigned(r) < unsigned(kTileR) ? off[v] + q * kTileS : kTileR * kTileS;
+                        atomicAdd(base + 2 * c, double(acc[q][v]));
+                    }
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[q] = typename M::V{R(0), R(0), R(0), R(0)};
         };
+        // the first records of the next tile, when this one's are all loaded
+        auto load_next = [&]() {
+            if (n0 + uint32_t(lane) < n1) nxt = rec[tile_record(T2, n0 + uint32_t(lane))];
+        };
+        if (q0 >= q1) {
+            load_next();
+            if constexpr (PREP) {
+                if (n0 + uint32_t(lane) < n1) nval = vis[nxt.idx & 0x7fffffffu];
+            }
+        }
         for (uint32_t base = q0; base < q1; base += 64) {
             const int n = __builtin_amdgcn_readfirstlane(int(min(64u, q1 - base)));
             // the lane's record: window, place in it, value
@@ -1113,7 +1142,7 @@ __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_ti
             };
             const int ou = place(dr, BUV, EUV), ov = place(ds, BUV, EUV), ot = place(dt, BT, ET);
             const int win = (dr - ou + 128) | ((ds - ov + 128) << 8) | ((dt - ot + 128) << 16);
-            const int places = ou | (ov << 4) | (ot << 8);
+            const int places = ou | (ov << 8) | (ot << 16);
             R nu0 = nxt.nu[0], nu1 = nxt.nu[1], nu2 = nxt.nu[2], v0 = nxt.v[0], v1 = nxt.v[1];
             if constexpr (PREP) {
                 const double vx = double(nval.x), vy = (nxt.idx & 0x80000000u) ? -double(nval.y) : double(nval.y);
@@ -1124,20 +1153,18 @@ __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_ti
             if (lane >= n) nu0 = nu1 = nu2 = v0 = v1 = R(0);        // finite weights, no value
             const int before = __shfl_up(win, 1, 64);
             const uint64_t moved = __ballot(lane < n && win != (lane == 0 ? cur : before));
-            vn += 64;
-            if constexpr (PREP) {
-                nxt = nxt2;
-                if (vn < q1) nval = vis[nxt.idx & 0x7fffffffu];
-                if (vn + 64 < q1) nxt2 = rec[seg_advance(sg, nseg, vn + 64, g)];
-            } else {
-                if (vn < q1) nxt = rec[seg_advance(sg, nseg, vn, g)];
-            }
+            const bool last = base + 64 >= q1;
+            const bool load = last ? n0 + uint32_t(lane) < n1 : base + 64 + uint32_t(lane) < q1;
+            if (last) load_next();
+            else if (load) nxt = rec[tile_record(T, base + 64 + uint32_t(lane))];
+            // the values of those records are asked for once they have come
+            const int vis_at = (min(n, 32) - 1) & ~7;
             for (int b0 = 0; b0 < n; b0 += WB) {
                 {
                     const int from = b0 + slot;
                     const R a0 = lane_read(nu0, from), a1 = lane_read(nu1, from), a2 = lane_read(nu2, from);
                     const R x = lane_read(v0, from), y = lane_read(v1, from);
-                    const int pl = lane_read(places, from);
+                    const int pl = (lane_read(places, from) + h * 0x010101) & 0x070707;
                     R hu = creg[D], hv = creg[D], ht = SAME ? creg[D] : czreg[D];
 #pragma unroll
                     for (int k = D - 1; k >= 0; --k) {
@@ -1145,11 +1172,11 @@ __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_ti
                         hv = hv * a1 + creg[k];
                         ht = ht * a2 + (SAME ? creg[k] : czreg[k]);
                     }
-                    const int pu = ((pl & 15) + h) & 7, pv = (((pl >> 4) & 15) + h) & 7, pt = ((pl >> 8) + h) & 7;
-                    my[(pu & 1) * 4 + (pu >> 1)] = h < W ? hu : R(0);
-                    my[8 + pv] = h < W ? hv : R(0);
-                    my[16 + 2 * pt] = h < WZ ? x * ht : R(0);
-                    my[17 + 2 * pt] = h < WZ ? y * ht : R(0);
+                    my[pl & 255] = hu;
+                    my[8 + ((pl >> 8) & 255)] = hv;
+                    R* mb = my + 16 + 2 * (pl >> 16);
+                    mb[0] = x * ht;
+                    mb[1] = y * ht;
                 }
                 wave_sync();
 #pragma unroll
@@ -1182,16 +1209,30 @@ __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_ti
                     }
                 }
                 wave_sync();
+                if constexpr (PREP) {
+                    if (b0 == vis_at && load) nval = vis[nxt.idx & 0x7fffffffu];
+                }
             }
         }
-        flush();
-    }
-    __syncthreads();
-    // write the tile: rows of kTileS cells
-    for (int i = tid; i < nt_valid * kTileR * kTileS; i += NT) {
-        const int c = i % (kTileR * kTileS), tt = i / (kTileR * kTileS);
-        const double* at = cells + tt * LT + 2 * c;
-        stack[tile_base(P, t0 - P.pl0 + tt, br, bs) * (kTileR * kTileS) + c] = cpx<R>{R(at[0]), R(at[1])};
+        if (cur >= 0) flush();
+        __syncthreads();
+        // write the tile and clear it for the next one
+        cpx<R>* dst = stack + tile_base(P, t0 - P.pl0, br, bs) * (kTileR * kTileS);
+        const size_t layer = size_t(P.nbr) * P.nbs * (kTileR * kTileS);
+        constexpr int LAYERS = NT / (kTileR * kTileS);       // layers written at a time
+        static_assert(NT % (kTileR * kTileS) == 0, "a thread keeps its cell of every layer");
+        const int c = tid % (kTileR * kTileS);
+        for (int tt = tid / (kTileR * kTileS); tt < nt_valid; tt += LAYERS) {
+            double2* at = reinterpret_cast<double2*>(cells + tt * LT + 2 * c);
+            const double2 z = *at;
+            dst[tt * layer + c] = cpx<R>{R(z.x), R(z.y)};
+            *at = double2{0.0, 0.0};
+        }
+        if (!more) break;
+        run.place += run.step;
+        q0 = n0;
+        q1 = n1;
+        __syncthreads();
     }
 }
 
@@ -1217,9 +1258,7 @@ struct GatherCfg {
 // spill a little and run 1.5x faster (FP32 is at four waves either way).
 template <typename R, int W, int WZ, bool SAME>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_degrid_tiles(const Rec<R>* __restrict__ rec,
-                                                      const uint32_t* __restrict__ start,
-                                                      const uint32_t* __restrict__ cls,
-                                                      const uint32_t* __restrict__ tlist,
+                                                      const TileRec* __restrict__ tlist,
                                                       const uint32_t* __restrict__ tpos, DevParams P,
                                                       const R* __restrict__ coef_g,
                                                       const R* __restrict__ coefz_g,
@@ -1231,33 +1270,30 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     __shared__ cpx<R> g[G::kLen];
     __shared__ R coef[W * (D + 1)];
     __shared__ R coefz[SAME ? 1 : WZ * (D + 1)];
-    __shared__ TileSegs sg;
 
-    const int tile = tile_of_block(P, tlist, tpos);
-    if (tile < 0) return;     // only occupied tiles are visited
+    const int place = tile_of_block(P, tpos);
+    if (place < 0) return;     // only occupied tiles are visited
+    const TileRec& T = tlist[place];
+    const int tile = int(T.tile);
     const int br = tile % P.nbr, bs = (tile / P.nbr) % P.nbs, bt = tile / (P.nbr * P.nbs);
     const int r0 = br * kTileR, s0 = bs * kTileS, t0 = bt * kTileT;
     const int nt_valid = min(kTileT, P.n_layers - t0 % (P.nbt * kTileT));   // layers of its channel
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    if (tid < 64) tile_segments(start, cls, P, bt, bs, br, sg);
     for (int i = tid; i < W * (D + 1); i += 256) coef[i] = coef_g[i];
     if (!SAME)
         for (int i = tid; i < WZ * (D + 1); i += 256) coefz[i] = coefz_g[i];
     __syncthreads();
-    const int nseg = sg.n;
-    const uint32_t total = sg.off[nseg];
+    const uint32_t total = T.total;
     if (total == 0) return;     // a tile no visibility reaches is not read at all
     const uint32_t quarter = (total + 3) / 4;
     const uint32_t q0 = min(total, quarter * uint32_t(wv)), q1 = min(total, q0 + quarter);
 
     Rec<R> nxt;
     uint32_t nxt_p = 0, nxt_m = 0;
-    int g_ = 0;
     if (q0 + uint32_t(lane) < q1) {
-        nxt_p = seg_advance(sg, nseg, q0 + uint32_t(lane), g_);
-        nxt_m = sg.nbr[g_];
+        nxt_p = tile_record(T, q0 + uint32_t(lane), nxt_m);
         nxt = rec[nxt_p];
     }
     for (int i = tid; i < G::kLen; i += 256) {
@@ -1283,8 +1319,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
         const uint32_t p = nxt_p, m = nxt_m;
         const uint32_t vn = base + WB + uint32_t(lane);
         if (vn < q1) {
-            nxt_p = seg_advance(sg, nseg, vn, g_);
-            nxt_m = sg.nbr[g_];
+            nxt_p = tile_record(T, vn, nxt_m);
             nxt = rec[nxt_p];
         }
         if (!live) continue;

@@ -28,8 +28,7 @@ bool tiles_supported(int W, int Wz, bool same);
 // non-null when rec holds a shared binning's degridding records, whose values
 // the scatter then takes from vis.
 template <typename R>
-bool launch_tiles(bool grid, int W, int Wz, bool same, int nblocks, const Rec<R>* rec, const uint32_t* start,
-                  const uint32_t* cls, const uint32_t* tlist, const uint32_t* tpos, const DevParams& P,
+bool launch_tiles(bool grid, int W, int Wz, bool same, int nblocks, const Rec<R>* rec, const TileRec* tlist, const uint32_t* tpos, const DevParams& P,
                   const R* coef, const R* coefz, const cpx<R>* vis, cpx<R>* stack, cpx<R>* part, size_t part_stride,
                   hipStream_t s);
 

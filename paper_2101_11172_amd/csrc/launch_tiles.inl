@@ -17,38 +17,36 @@ namespace wsg {
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
 template <typename R, int W, int WZ, bool SAME>
-void launch_tiles_w(bool grid, int nblocks, const Rec<R>* rec, const uint32_t* start, const uint32_t* cls,
-                    const uint32_t* tlist, const uint32_t* tpos, const DevParams& P, const R* coef, const R* coefz,
+void launch_tiles_w(bool grid, int nblocks, const Rec<R>* rec, const TileRec* tlist, const uint32_t* tpos, const DevParams& P, const R* coef, const R* coefz,
                     const cpx<R>* vis, cpx<R>* stack, cpx<R>* part, size_t part_stride, hipStream_t s) {
     if (grid && W <= kWin) {
         // the matrix kernel, wherever the window of 8 cells holds the support
         if constexpr (W <= kWin) {
             constexpr int TH = MatScatterCfg<R, W, WZ>::kThreads;
             if (vis)
-                hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec, start,
-                                   cls, tlist, tpos, P, coef, coefz, vis, stack);
+                hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec,
+                                   tlist, tpos, P, coef, coefz, vis, stack);
             else
-                hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec, start,
-                                   cls, tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
+                hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec,
+                                   tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
         }
     } else if (grid) {
         if constexpr (W > kWin) {
             constexpr int TH = ScatterCfg<R, W, WZ>::kThreads;
             if (vis)
-                hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec, start, cls,
+                hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec,
                                    tlist, tpos, P, coef, coefz, vis, stack);
             else
-                hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec, start, cls,
+                hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec,
                                    tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
         }
     } else
-        hipLaunchKernelGGL((k_degrid_tiles<R, W, WZ, SAME>), dim3(nblocks), dim3(256), 0, s, rec, start, cls, tlist,
+        hipLaunchKernelGGL((k_degrid_tiles<R, W, WZ, SAME>), dim3(nblocks), dim3(256), 0, s, rec, tlist,
                            tpos, P, coef, coefz, (const cpx<R>*)stack, part, part_stride);
 }
 
 template <typename R>
-bool launch_tiles(bool grid, int W, int Wz, bool same, int nblocks, const Rec<R>* rec, const uint32_t* start,
-                  const uint32_t* cls, const uint32_t* tlist, const uint32_t* tpos, const DevParams& P,
+bool launch_tiles(bool grid, int W, int Wz, bool same, int nblocks, const Rec<R>* rec, const TileRec* tlist, const uint32_t* tpos, const DevParams& P,
                   const R* coef, const R* coefz, const cpx<R>* vis, cpx<R>* stack, cpx<R>* part, size_t part_stride,
                   hipStream_t s) {
     if (same) {
@@ -56,7 +54,7 @@ bool launch_tiles(bool grid, int W, int Wz, bool same, int nblocks, const Rec<R>
         switch (W) {
 #define WSG_SAME(w)                                                                                          \
     case w:                                                                                                   \
-        launch_tiles_w<R, w, w, true>(grid, nblocks, rec, start, cls, tlist, tpos, P, coef, coefz, vis, stack,  \
+        launch_tiles_w<R, w, w, true>(grid, nblocks, rec, tlist, tpos, P, coef, coefz, vis, stack,  \
                                       part, part_stride, s);                                                  \
         return true;
             WSG_SAME_WIDTHS(WSG_SAME)
@@ -66,7 +64,7 @@ bool launch_tiles(bool grid, int W, int Wz, bool same, int nblocks, const Rec<R>
     }
 #define WSG_OWN(w, wz)                                                                                          \
     if (W == w && Wz == wz) {                                                                                 \
-        launch_tiles_w<R, w, wz, false>(grid, nblocks, rec, start, cls, tlist, tpos, P, coef, coefz, vis, stack, \
+        launch_tiles_w<R, w, wz, false>(grid, nblocks, rec, tlist, tpos, P, coef, coefz, vis, stack, \
                                         part, part_stride, s);                                                  \
         return true;                                                                                           \
     }

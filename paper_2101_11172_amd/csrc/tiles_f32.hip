@@ -12,8 +12,7 @@ bool tiles_supported(int W, int Wz, bool same) {
     return false;
 }
 
-template bool launch_tiles<float>(bool, int, int, bool, int, const Rec<float>*, const uint32_t*, const uint32_t*,
-                                  const uint32_t*, const uint32_t*, const DevParams&, const float*, const float*,
+template bool launch_tiles<float>(bool, int, int, bool, int, const Rec<float>*, const TileRec*, const uint32_t*, const DevParams&, const float*, const float*,
                                   const cpx<float>*, cpx<float>*, cpx<float>*, size_t, hipStream_t);
 
 }  // namespace wsg

@@ -182,7 +182,7 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     L.rows = off;    off += al256(size_t(nch) * p->nbt * p->nbr);
     L.mask = off;    off += al256(size_t(nch) * p->nbt * p->nbr * mask_words(p->nbs) * 4);
     L.tpos = off;    off += al256(size_t(L.nbins + 1) * 4);
-    L.tlist = off;   off += al256(size_t(L.nbins) * 4);
+    L.tlist = off;   off += al256(std::min(size_t(L.nbins), 8 * size_t(M)) * sizeof(TileRec));   // a record reaches 8 tiles at most
     L.chan = off;    off += al256(sizeof(long long) * (kMaxChannels + 1)) + al256(sizeof(int) * (kMaxChannels + 1));
     // the large buffers start on 2 MiB boundaries (their power-of-two line
     // strides then meet the memory channels the same way whatever precedes them)
@@ -299,7 +299,7 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
     auto* rows = reinterpret_cast<uint8_t*>(w + L.rows);
     auto* mask = reinterpret_cast<uint32_t*>(w + L.mask);
     auto* tpos = reinterpret_cast<uint32_t*>(w + L.tpos);
-    auto* tlist = reinterpret_cast<uint32_t*>(w + L.tlist);
+    auto* tlist = reinterpret_cast<TileRec*>(w + L.tlist);
     auto* coff = reinterpret_cast<long long*>(w + L.chan);
     auto* cblk = reinterpret_cast<int*>(w + L.chan + al256(sizeof(long long) * (kMaxChannels + 1)));
     auto* skipped = reinterpret_cast<uint32_t*>(w + L.skipped);
@@ -341,7 +341,7 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
                            (const uint32_t*)cls, P, occ, rows, mask, count);
         scan(count, tpos, bsums, L.nbins, s);
         hipLaunchKernelGGL(k_tile_list, dim3((L.nbins + 255) / 256), dim3(256), 0, s, (const uint8_t*)occ,
-                           (const uint32_t*)tpos, L.nbins, tlist);
+                           (const uint32_t*)tpos, (const uint32_t*)start, (const uint32_t*)cls, P, tlist);
     }
 }
 
@@ -357,11 +357,10 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
     auto* stack = reinterpret_cast<cpx<R>*>(w + L.stack);
     auto* inter = reinterpret_cast<cpx<R>*>(w + L.inter);
     auto* start = reinterpret_cast<uint32_t*>(w + L.start);
-    auto* cls = reinterpret_cast<uint32_t*>(w + L.cls);
     auto* rows = reinterpret_cast<uint8_t*>(w + L.rows);
     auto* mask = reinterpret_cast<uint32_t*>(w + L.mask);
     auto* tpos = reinterpret_cast<uint32_t*>(w + L.tpos);
-    auto* tlist = reinterpret_cast<uint32_t*>(w + L.tlist);
+    auto* tlist = reinterpret_cast<TileRec*>(w + L.tlist);
     const bool f64 = sizeof(R) == 8;
     const R* coef = f64 ? reinterpret_cast<const R*>(plan->poly64) : reinterpret_cast<const R*>(plan->poly32);
     const R* coefz = f64 ? reinterpret_cast<const R*>(plan->polyz64) : reinterpret_cast<const R*>(plan->polyz32);
@@ -384,7 +383,7 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
         if (grid) {
             {
                 StageMark mark(s, 1);
-                launch_tiles<R>(true, P.W, P.Wz, plan->same_design, nblocks, rec, start, cls, tlist, tpos, Q, coef,
+                launch_tiles<R>(true, P.W, P.Wz, plan->same_design, nblocks, rec, tlist, tpos, Q, coef,
                                 coefz, prep_vis, stack, nullptr, 0, s);
             }
             launch_fft<R>(true, Q, mask, rows, stack, inter, tw, corr, nullptr, static_cast<R*>(out), s);
@@ -392,7 +391,7 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
             launch_fft<R>(false, Q, mask, rows, stack, inter, tw, corr, static_cast<const R*>(in), nullptr, s);
             if (M > 0) {
                 StageMark mark(s, 7);
-                launch_tiles<R>(false, P.W, P.Wz, plan->same_design, nblocks, rec, start, cls, tlist, tpos, Q, coef,
+                launch_tiles<R>(false, P.W, P.Wz, plan->same_design, nblocks, rec, tlist, tpos, Q, coef,
                                 coefz, nullptr, stack, part, size_t(M), s);
             }
         }
