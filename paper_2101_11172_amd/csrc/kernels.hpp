@@ -1236,7 +1236,238 @@ __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_ti
     }
 }
 
-// Gather: lanes over records.  The tile sits in LDS as complex cells, rows
+// FP64 gather for W <= 8: for the records k of one window
+//     out_k = sum_a wt_k(a) sum_(x, y) [wu_k(x) wv_k(y)] cell(x, y, a)
+// the inner sums are a product of a K x 64 matrix (rows 16 records, columns the
+// window's pairs (x, y)) with a 64 x 16 one (columns the 8 layers times real and
+// imaginary), at most 16 matrix instructions of 16 x 16 x 4 per 16 records of a
+// window; rows x of the window outside the tile are left out (a window at a
+// tile's edge belongs to several tiles).  Rows that hold another window's record
+// are computed and dropped.  The weights by layer and the sum over the layers
+// follow on the vector units.  A wave stages kSlots records at a time as the
+// scatter does.  Against a lane per record (k_degrid_tiles): wide field 2.80 ->
+// 1.59 ms, 46,332 visibilities at 512^2 102 -> 63 us, 1,531 scattered ones 27 ->
+// 16 us.  In FP32 a lane per record stays: half the LDS bytes and twice the
+// vector rate make it the better one wherever a window holds few records
+// (4096^2, 3 per window: 6.0 against 8.8 ms; 768^2, W = 6: 0.09 against 0.16)
+// and as good where it holds 28 (wide field: 1.41 against 1.46).
+template <typename R>
+struct MatGatherCfg {
+    static constexpr int kWaves = 4;                             // two blocks per CU (80 KB of LDS)
+    static constexpr int kThreads = 64 * kWaves;
+    static constexpr int kSlots = 16;                            // records staged at a time
+    static constexpr int kSlot = 26;                             // values between slots (8 wu, 8 wv, 8 wt, padding)
+    static constexpr int kLT = kTileR * kTileS + 2;              // cells between layers: a window's layers meet
+                                                                 // distinct banks
+};
+template <typename R, int W>
+constexpr bool mat_gather() {
+    return sizeof(R) == 8 && W <= kWin;
+}
+
+// x of the lane n places back in its row of 16 (rotating)
+template <int N>
+__device__ __forceinline__ double row_ror(double x) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + N, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x120 + N, 0xf, 0xf, true));
+}
+
+template <typename R, int W, int WZ, bool SAME>
+__global__ void __launch_bounds__((MatGatherCfg<R>::kThreads)) __attribute__((amdgpu_waves_per_eu(2)))
+    k_degrid_tiles_mat(const Rec<R>* __restrict__ rec, const TileRec* __restrict__ tlist,
+                       const uint32_t* __restrict__ tpos, DevParams P, const R* __restrict__ coef_g,
+                       const R* __restrict__ coefz_g, const cpx<R>* __restrict__ stack, cpx<R>* __restrict__ part,
+                       size_t part_stride) {
+    using Cfg = MatGatherCfg<R>;
+    using M = Mfma<R>;
+    constexpr int D = KernelDegree<R>::value, NW = Cfg::kWaves, NT = Cfg::kThreads, NS = Cfg::kSlots, LT = Cfg::kLT;
+    constexpr int EUV = window_edge(W), ET = window_edge(WZ), BUV = 17 - W, BT = 17 - WZ;
+    constexpr int STEP = NT / (kTileR * kTileS), PER = kTileT / STEP;        // a thread's cells: layers tl + STEP i
+    static_assert(W <= kWin && WZ <= W && NT % (kTileR * kTileS) == 0, "a thread keeps its cell of every layer");
+    __shared__ __align__(16) cpx<R> cells[kTileT * LT];          // [t][r][s]
+    __shared__ __align__(16) R stage[NW * NS * Cfg::kSlot];
+
+    TileRun run;
+    if (!tiles_of_block(P, tpos, 512, run)) return;      // only occupied tiles are visited
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto part_of = [&](uint32_t total, uint32_t& q0, uint32_t& q1) {         // this wave's part of a tile's list
+        const uint32_t each = (total + NW - 1) / NW;
+        q0 = min(total, each * uint32_t(wv));
+        q1 = min(total, q0 + each);
+    };
+    // staging: lane (record lane % 8, segment h); segments past the width are zero
+    const int slot = lane & 7, h = lane >> 3;
+    R creg[D + 1], czreg[SAME ? 1 : D + 1];
+#pragma unroll
+    for (int k = 0; k <= D; ++k) {
+        creg[k] = h < W ? coef_g[h * (D + 1) + k] : R(0);
+        if constexpr (!SAME) czreg[k] = h < WZ ? coefz_g[h * (D + 1) + k] : R(0);
+    }
+    // the tile's cells in the order pass A stored them
+    const int e = tid % (kTileR * kTileS), tl = tid / (kTileR * kTileS);
+    const size_t layer = size_t(P.nbr) * P.nbs * (kTileR * kTileS);
+    cpx<R> cr[PER];
+    auto load_cells = [&](int tile) {
+        const int br = tile % P.nbr, bs = (tile / P.nbr) % P.nbs, t0 = tile / (P.nbr * P.nbs) * kTileT;
+        const int nt_valid = min(kTileT, P.n_layers - t0 % (P.nbt * kTileT));
+        const cpx<R>* src = stack + tile_base(P, t0 - P.pl0, br, bs) * (kTileR * kTileS) + e;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int tt = tl + STEP * i;
+            cr[i] = tt < nt_valid ? src[tt * layer] : cpx<R>{R(0), R(0)};
+        }
+    };
+    uint32_t q0, q1;
+    part_of(tlist[run.place].total, q0, q1);
+    Rec<R> nxt{};              // the lane's record of the next 64, its index and tile set
+    uint32_t nxt_p = 0, nxt_m = 0;
+    auto load_rec = [&](const TileRec& T, uint32_t v) {
+        nxt_p = tile_record(T, v, nxt_m);
+        nxt = rec[nxt_p];
+    };
+    if (q0 + uint32_t(lane) < q1) load_rec(tlist[run.place], q0 + uint32_t(lane));
+    load_cells(int(tlist[run.place].tile));
+    R* st = stage + wv * (NS * Cfg::kSlot);
+    for (int i = lane; i < NS * Cfg::kSlot; i += 64) st[i] = R(0);
+    // operands: lane (g, i) holds A row i (record), and B column i = 2 a + c; the
+    // matrix step (x, half) joins the pairs (x, 4 half + g)
+    const int g = lane >> 4, i16 = lane & 15;
+
+    for (;;) {
+        const TileRec& T = tlist[run.place];
+        const int tile = int(T.tile);
+        const int br = tile % P.nbr, bs = (tile / P.nbr) % P.nbs, bt = tile / (P.nbr * P.nbs);
+        const int r0 = br * kTileR, s0 = bs * kTileS, t0 = bt * kTileT;
+        const bool more = run.place + run.step < run.end;
+        const TileRec& T2 = tlist[more ? run.place + run.step : run.place];
+        uint32_t n0 = 0, n1 = 0;
+        if (more) part_of(T2.total, n0, n1);
+        {
+            int rr, ss;
+            degrid_place(e, bs, P.classes, rr, ss);
+            cpx<R>* dst = cells + rr * kTileS + ss - s0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) dst[(tl + STEP * i) * LT] = cr[i];
+        }
+        __syncthreads();
+        if (more) load_cells(int(T2.tile));
+        if (q0 >= q1 && n0 + uint32_t(lane) < n1) load_rec(T2, n0 + uint32_t(lane));
+        int cur = -1;                // the window whose cells are in b, packed
+        R b[2 * kWin];
+        for (uint32_t base = q0; base < q1; base += 64) {
+            const int n = __builtin_amdgcn_readfirstlane(int(min(64u, q1 - base)));
+            const int dr = wrap_offset(int(nxt.ruv & 0xffffu), r0, P.Np);
+            const int ds = wrap_offset(int(nxt.ruv >> 16), s0, P.Np);
+            const int dt = int(nxt.rt) - t0;
+            auto place = [](int d, int B, int edge) {
+                const int l = d & (kTileR - 1);
+                return (l >= B ? l - B : l) % edge;
+            };
+            const int ou = place(dr, BUV, EUV), ov = place(ds, BUV, EUV), ot = place(dt, BT, ET);
+            const int win = (dr - ou + 128) | ((ds - ov + 128) << 8) | ((dt - ot + 128) << 16);
+            const int places = ou | (ov << 8) | (ot << 16);
+            R nu0 = nxt.nu[0], nu1 = nxt.nu[1], nu2 = nxt.nu[2];
+            if (lane >= n) nu0 = nu1 = nu2 = R(0);                  // finite weights
+            // where this tile's part of the record goes: the slot of the tile's offset
+            // from the record's own bin (no two tiles share a slot)
+            const unsigned long long to = (unsigned long long)nxt_m * part_stride + nxt_p;
+            const int to_lo = int(uint32_t(to)), to_hi = int(uint32_t(to >> 32));
+            const int before = __shfl_up(win, 1, 64);
+            const uint64_t moved = __ballot(lane > 0 && lane < n && win != before);
+            if (base + 64 >= q1) {
+                if (n0 + uint32_t(lane) < n1) load_rec(T2, n0 + uint32_t(lane));
+            } else if (base + 64 + uint32_t(lane) < q1) {
+                load_rec(T, base + 64 + uint32_t(lane));
+            }
+            for (int b0 = 0; b0 < n; b0 += NS) {
+                const int ns = min(NS, n - b0);
+                for (int p = 0; p < ns; p += 8) {
+                    const int from = b0 + p + slot;
+                    const R a0 = lane_read(nu0, from), a1 = lane_read(nu1, from), a2 = lane_read(nu2, from);
+                    const int pl = (lane_read(places, from) + h * 0x010101) & 0x070707;
+                    R hu = creg[D], hv = creg[D], ht = SAME ? creg[D] : czreg[D];
+#pragma unroll
+                    for (int k = D - 1; k >= 0; --k) {
+                        hu = hu * a0 + creg[k];
+                        hv = hv * a1 + creg[k];
+                        ht = ht * a2 + (SAME ? creg[k] : czreg[k]);
+                    }
+                    R* my = st + (p + slot) * Cfg::kSlot;
+                    my[pl & 255] = hu;
+                    my[8 + ((pl >> 8) & 255)] = hv;
+                    my[16 + (pl >> 16)] = ht;
+                }
+                wave_sync();
+                const uint64_t mv = moved >> b0;
+                for (int j = 0; j < ns;) {
+                    // the next records of one window: [j, end)
+                    const uint64_t rest = mv >> (j + 1);
+                    const int end = min(min(j + 16, ns), rest ? j + 1 + int(__builtin_ctzll(rest)) : ns);
+                    const int w = __builtin_amdgcn_readlane(win, b0 + j);
+                    const int wr = (w & 255) - 128, ws = ((w >> 8) & 255) - 128, wt = ((w >> 16) & 255) - 128;
+                    const bool lo = ws > -4, hi = ws < kTileS - 4;       // the window's halves in v that meet the tile
+                    if (w != cur) {
+                        cur = w;
+                        const int t = wt + (i16 >> 1), s = ws + g;
+                        const bool tok = unsigned(t) < unsigned(kTileT);
+                        const bool ok0 = tok && unsigned(s) < unsigned(kTileS), ok1 = tok && unsigned(s + 4) < unsigned(kTileS);
+                        const R* base_c = reinterpret_cast<const R*>(cells) + (i16 & 1);
+                        const int c0 = ok0 ? t * LT + s : 0, c1 = ok1 ? t * LT + s + 4 : 0;
+#pragma unroll
+                        for (int x = 0; x < kWin; ++x) {
+                            if (unsigned(wr + x) < unsigned(kTileR)) {
+                                const int row = (wr + x) * kTileS;
+                                const R y0 = base_c[2 * (c0 + row)], y1 = base_c[2 * (c1 + row)];
+                                b[2 * x] = ok0 ? y0 : R(0);
+                                b[2 * x + 1] = ok1 ? y1 : R(0);
+                            }
+                        }
+                    }
+                    const R* row = st + min(j + i16, NS - 1) * Cfg::kSlot;
+                    R wu[kWin];
+#pragma unroll
+                    for (int x = 0; x < kWin; ++x) wu[x] = row[x];
+                    const R v0 = row[8 + g], v1 = row[12 + g];
+                    typename M::V d0{R(0), R(0), R(0), R(0)}, d1{R(0), R(0), R(0), R(0)};
+#pragma unroll
+                    for (int x = 0; x < kWin; ++x) {
+                        if (unsigned(wr + x) < unsigned(kTileR)) {
+                            if (lo) d0 = M::mul(wu[x] * v0, b[2 * x], d0);
+                            if (hi) d1 = M::mul(wu[x] * v1, b[2 * x + 1], d1);
+                        }
+                    }
+                    // times the layer weights, summed over the layers: lane 2 v + c takes row v
+                    R out = R(0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+#pragma clang fp contract(off)
+                        R y = (d0[v] + d1[v]) * st[min(j + M::row(lane, v), NS - 1) * Cfg::kSlot + 16 + (i16 >> 1)];
+                        // in this order, without fused multiply-adds, every lane forms the same
+                        // sum, bit for bit: a record's result does not depend on its row
+                        y += row_ror<8>(y);
+                        y += row_ror<4>(y);
+                        y += row_ror<2>(y);
+                        out = (i16 >> 1) == v ? y : out;
+                    }
+                    const int k = M::row(lane, (i16 >> 1) & 3), from = b0 + j + k;
+                    const uint32_t plo = uint32_t(lane_read(to_lo, from & 63)), phi = uint32_t(lane_read(to_hi, from & 63));
+                    if (i16 < 8 && j + k < end)
+                        reinterpret_cast<R*>(part + (((unsigned long long)phi << 32) | plo))[i16 & 1] = out;
+                    j = end;
+                }
+                wave_sync();
+            }
+        }
+        if (!more) break;
+        run.place += run.step;
+        q0 = n0;
+        q1 = n1;
+        __syncthreads();
+    }
+}
+
+// Gather in FP32, and in FP64 for W > 8: lanes over records.  The tile sits in LDS as complex cells, rows
 // kLR = 17 cells and layers kLT = 16 kLR + 1 cells apart (the padding cells are
 // zero), with a zero guard of (kLR + 1)(W - 1) cells before and after, so that
 // for any support start (dr, ds) in [-(W-1), 15] the cell address

@@ -40,9 +40,13 @@ void launch_tiles_w(bool grid, int nblocks, const Rec<R>* rec, const TileRec* tl
                 hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec,
                                    tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
         }
-    } else
-        hipLaunchKernelGGL((k_degrid_tiles<R, W, WZ, SAME>), dim3(nblocks), dim3(256), 0, s, rec, tlist,
-                           tpos, P, coef, coefz, (const cpx<R>*)stack, part, part_stride);
+    } else if constexpr (mat_gather<R, W>()) {
+        hipLaunchKernelGGL((k_degrid_tiles_mat<R, W, WZ, SAME>), dim3(nblocks), dim3(MatGatherCfg<R>::kThreads), 0, s,
+                           rec, tlist, tpos, P, coef, coefz, (const cpx<R>*)stack, part, part_stride);
+    } else {
+        hipLaunchKernelGGL((k_degrid_tiles<R, W, WZ, SAME>), dim3(nblocks), dim3(256), 0, s, rec, tlist, tpos, P, coef,
+                           coefz, (const cpx<R>*)stack, part, part_stride);
+    }
 }
 
 template <typename R>
