@@ -120,6 +120,20 @@ __host__ __device__ constexpr PassATable pass_a_table(int Np) {
     return {F, second, radix, n, second + radix * n};
 }
 
+// Pass B's twiddle table behind pass A's: for a line of Np = 2^a or 3 2^a points
+// the twiddles of each pass after the first, [m][k < n], n the points joined
+// before the pass: its radix-16 passes, then that of radix 2, 4 or 8 (the
+// radix-3 pass reads the roots themselves).
+__host__ __device__ constexpr int line_table_size(int Np) {
+    const int p2 = Np % 3 == 0 ? Np / 3 : Np, l = log2_floor(p2);
+    int n = 16, size = 0;
+    for (int p = 1; p < l / 4; ++p, n *= 16) size += 16 * n;
+    return size + (l % 4 ? (1 << (l % 4)) * n : 0);
+}
+__host__ __device__ constexpr int line_table_at(int Np) {        // its place in the plan's table
+    return Np + pass_a_table(Np).entries + Np;
+}
+
 // Cells of one layer of a tile as the degrid direction stores them: class by
 // class (cell s of a line is of class s mod C), the 16 rows of the class's cells
 // of the tile each, so that a pass A block, which holds one class of the tile's

@@ -135,9 +135,9 @@ constexpr int log2_of() {
 
 // In-place FFT of one line; `buf` is this line's LDS buffer of LinePad<N>::size
 // elements.  Every thread of the block must call this the same number of times
-// (it contains __syncthreads).
+// (it contains __syncthreads).  tw: the plan's roots; tab: its pass B table.
 template <typename R, int N, int DIR>
-__device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx<R>* __restrict__ tw, int j) {
+__device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx<R>* tw, const cpx<R>* tab, int j) {
     constexpr bool R3 = N % 3 == 0;
     constexpr int NP2 = R3 ? N / 3 : N;               // power-of-two part
     constexpr int LOG2 = log2_of<NP2>();
@@ -153,9 +153,9 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
 #pragma unroll
             for (int m = 0; m < 16; ++m) v[m] = buf[lpad_at<T>(j, pj, m)];
             const int k = j & (Ns - 1);
-            const int stride = N / (Ns * 16);
 #pragma unroll
-            for (int m = 1; m < 16; ++m) v[m] = cmul(v[m], twiddle<R, DIR>(tw, k * m * stride));
+            for (int m = 1; m < 16; ++m) v[m] = cmul(v[m], twiddle<R, DIR>(tab, m * Ns + k));
+            tab += 16 * Ns;
         }
         dft16<R, DIR>(v);
         if (!R3 && REM == 0 && p == P16 - 1) return;   // natural order: v[m] = X[j + m T]
@@ -169,7 +169,6 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
     if constexpr (REM > 0) {
         constexpr int RR = 1 << REM;      // radix of this pass
         constexpr int B = 16 / RR;        // butterflies per thread, N / RR apart (Ns in the last pass)
-        constexpr int TWS = R3 ? 3 : 1;   // N / (Ns RR)
         cpx<R> u[16];
 #pragma unroll
         for (int b = 0; b < B; ++b)
@@ -179,7 +178,7 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
         for (int b = 0; b < B; ++b) {
             const int k = (j + b * T) & (Ns - 1);
 #pragma unroll
-            for (int m = 1; m < RR; ++m) u[b * RR + m] = cmul(u[b * RR + m], twiddle<R, DIR>(tw, k * m * TWS));
+            for (int m = 1; m < RR; ++m) u[b * RR + m] = cmul(u[b * RR + m], twiddle<R, DIR>(tab, m * Ns + k));
             if constexpr (RR == 2) dft2<R, DIR>(u[b * RR], u[b * RR + 1]);
             if constexpr (RR == 4) dft4<R, DIR>(u[b * RR], u[b * RR + 1], u[b * RR + 2], u[b * RR + 3]);
             if constexpr (RR == 8) dft8<R, DIR>(&u[b * RR]);

@@ -1849,11 +1849,15 @@ __device__ __forceinline__ uint32_t live_mask(const uint8_t* __restrict__ mark, 
 // (Algorithm 5 steps 3b-4), then the 3-D correction (step 5): dirty[q][p].
 // One launch covers a segment of P.pln consecutive layers of one channel: the
 // segment starts at layer seg0 of the pass's buffer and at layer tloc0 of the
-// channel; `accumulate` adds to the map instead of writing it.
+// channel; `accumulate` adds to the map instead of writing it.  Where the image
+// has too few rows to fill the chip, gridDim.y parts of the layers run in blocks
+// of their own and leave their uncorrected sums in `partial` ([part][N][N]) for
+// k_map_sum.
 template <typename R, int NP>
-__global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
+__global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T)) __attribute__((amdgpu_waves_per_eu(2)))
     k_grid_fft_b(const cpx<R>* __restrict__ inter, const uint8_t* __restrict__ rows, const cpx<R>* __restrict__ tw,
-                 const R* __restrict__ corr, R* __restrict__ dirty, DevParams P, int seg0, int tloc0, int accumulate) {
+                 const R* __restrict__ corr, R* __restrict__ dirty, R* __restrict__ partial, DevParams P, int seg0,
+                 int tloc0, int accumulate) {
     using C = FftCfg<R, NP>;
     constexpr int Np = C::N, T = C::T, NL = C::kNLr, LP = LinePad<Np>::size;
     __shared__ cpx<R> buf[NL * LP];
@@ -1865,13 +1869,13 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
     cpx<R>* lbuf = buf + line * LP;
     double z[16];
     R acc[16];
-    int pix[16];
+    uint32_t in = 0;        // bit k: bin j + T k is an image column
     const double m = double(qq - half) * P.dl;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         const int f = j + T * k;
         const int p = shift_half<Np>(f, half);
-        pix[k] = (row_ok && p < N) ? p : -1;
+        in |= uint32_t(row_ok && p < N) << k;
         const double l = double(min(p, N - 1) - half) * P.dl;   // bins outside the image are not used
         const double r2 = l * l + m * m;
         const double nm1 = -r2 / (1.0 + sqrt(1.0 - r2));     // n - 1
@@ -1882,7 +1886,8 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
     // in the current tile layer (the others are zero and not stored)
     uint32_t live = 0;
     int live_layer = -1;
-    for (int t = 0; t < P.pln; ++t) {
+    const int per = (P.pln + gridDim.y - 1) / gridDim.y, t1 = min(P.pln, int(blockIdx.y + 1) * per);
+    for (int t = blockIdx.y * per; t < t1; ++t) {
         const cpx<R>* src = inter + ((size_t)(seg0 + t) * inter_blocks(N) + (qq >> 4)) * (P.nbr * 256) + (qq & 15) * 16;
         const int tile_layer = __builtin_amdgcn_readfirstlane((P.pl0 + seg0 + t) / kTileT);
         if (tile_layer != live_layer) {
@@ -1892,11 +1897,16 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
         cpx<R> v[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) v[k] = (live >> k) & 1u ? src[inter_cell(j + T * k)] : cpx<R>{R(0), R(0)};
-        fft_line<R, NP, +1>(v, lbuf, tw, j);
+        // FP64 reads the twiddles again for each layer: kept in registers across the layers
+        // (30 of them) they left one wave per SIMD (wide field: grid 2.15 -> 1.94 ms, degrid
+        // 2.10 -> 1.69).  In FP32 they stay (read again: 0.78 -> 0.86 and 0.71 -> 0.86 ms).
+        const cpx<R>*root = tw, *tab = tw + line_table_at(NP);
+        if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(root), "+s"(tab));
+        fft_line<R, NP, +1>(v, lbuf, root, tab, j);
         const double tl = double(tloc0 + t + P.t_lo) + P.tphase;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            if (pix[k] >= 0) {
+            if ((in >> k) & 1u) {
                 R s, c;
                 phase_turns(tl * z[k], &s, &c);
                 acc[k] += v[k].x * c - v[k].y * s;
@@ -1904,19 +1914,40 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
         }
     }
     if (!row_ok) return;
+    if (gridDim.y > 1) {
+        R* out = partial + (size_t(blockIdx.y) * N + q) * N;
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if ((in >> k) & 1u) out[shift_half<Np>(j + T * k, half)] = acc[k];
+        return;
+    }
     // the channel's first layer segment writes the map, later ones add to it
 #pragma unroll
     for (int k = 0; k < 16; ++k)
-        if (pix[k] >= 0) {
-            const size_t o = (size_t)q * N + pix[k];
+        if ((in >> k) & 1u) {
+            const size_t o = (size_t)q * N + shift_half<Np>(j + T * k, half);
             const R d = acc[k] * corr[o];
             dirty[o] = accumulate ? dirty[o] + d : d;
         }
 }
 
+// Sum of the parts that a split pass B left, and the correction.
+template <typename R>
+__global__ void __launch_bounds__(256) k_map_sum(const R* __restrict__ partial, int parts, const R* __restrict__ corr,
+                                                 R* __restrict__ dirty, int n, int accumulate) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    R a = R(0);
+#pragma unroll 4
+    for (int p = 0; p < parts; ++p) a += partial[size_t(p) * n + i];
+    const R d = a * corr[i];
+    dirty[i] = accumulate ? dirty[i] + d : d;
+}
+
 // degrid pass B': for each image row q and layer t: f h_x h_y h_z exp(-i 2 pi t z)
 // zero-padded along p, FFT along p -> intermediate [t][q][r] (Algorithm 6 steps 2-3).
-// Segments of one channel's layers as for k_grid_fft_b.
+// Segments of one channel's layers as for k_grid_fft_b; gridDim.y parts of the
+// layers run in blocks of their own.
 template <typename R, int NP>
 __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
     k_degrid_fft_b(const R* __restrict__ image, const R* __restrict__ corr, const cpx<R>* __restrict__ tw,
@@ -1946,7 +1977,8 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
     }
     uint32_t live = 0;
     int live_layer = -1;
-    for (int t = 0; t < P.pln; ++t) {
+    const int per = (P.pln + gridDim.y - 1) / gridDim.y, t1 = min(P.pln, int(blockIdx.y + 1) * per);
+    for (int t = blockIdx.y * per; t < t1; ++t) {
         const double tl = double(tloc0 + t + P.t_lo) + P.tphase;
         cpx<R> v[16];
 #pragma unroll
@@ -1955,7 +1987,9 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
             phase_turns(-tl * z[k], &s, &c);
             v[k] = cpx<R>{g[k] * c, g[k] * s};
         }
-        fft_line<R, NP, -1>(v, lbuf, tw, j);
+        const cpx<R>*root = tw, *tab = tw + line_table_at(NP);
+        if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(root), "+s"(tab));     // as in k_grid_fft_b
+        fft_line<R, NP, -1>(v, lbuf, root, tab, j);
         if (row_ok) {
             // only frequencies r of rows of tiles with an occupied tile are used later
             const int tile_layer = __builtin_amdgcn_readfirstlane((P.pl0 + seg0 + t) / kTileT);

@@ -22,6 +22,13 @@ void launch_fft_n(bool grid, const DevParams& P, const uint32_t* mask, const uin
     const unsigned grid_b = unsigned((P.N + C::kNLr - 1) / C::kNLr);
     const int chl = P.nbt * kTileT;
     const size_t map = size_t(P.N) * size_t(P.N);
+    // Pass B walks the layers of a row in one block, about 3 us a layer however few
+    // blocks there are.  Where they do not fill the chip (eight waves on a CU) the
+    // layers are split, as far as the blocks still run at the same time: beyond
+    // that each more part repeats the row's set-up (1024^2 FP32, 512 blocks in two
+    // parts: 88 -> 93 us).  FP64 at 192 x 192: 51 -> 13 us, FP32 at 512 x 512 37 -> 15.
+    constexpr int kFill = 256 * std::max(1, 512 / (C::kNLr * C::T));
+    auto parts = [&](int layers) { return std::max(1, std::min(layers, kFill / int(grid_b))); };
     auto segments = [&](auto&& fn) {
         for (int c = P.pl0 / chl; c < P.nch && c * chl < P.pl0 + P.pln; ++c) {
             const int lo = std::max(P.pl0, c * chl), hi = std::min(P.pl0 + P.pln, c * chl + P.n_layers);
@@ -38,9 +45,14 @@ void launch_fft_n(bool grid, const DevParams& P, const uint32_t* mask, const uin
         segments([&](int c, int lo, int hi) {
             DevParams Q = P;
             Q.pln = hi - lo;
-            hipLaunchKernelGGL((k_grid_fft_b<R, NP>), dim3(grid_b), dim3(C::kNLr * C::T), 0, s,
-                               (const cpx<R>*)inter, rows, tw, corr, dirty + size_t(c) * map, Q, lo - P.pl0,
-                               lo - c * chl, lo > c * chl ? 1 : 0);
+            const int S = parts(Q.pln), acc = lo > c * chl ? 1 : 0;
+            R* partial = reinterpret_cast<R*>(stack);        // pass A has read it
+            hipLaunchKernelGGL((k_grid_fft_b<R, NP>), dim3(grid_b, S), dim3(C::kNLr * C::T), 0, s,
+                               (const cpx<R>*)inter, rows, tw, corr, dirty + size_t(c) * map, partial, Q, lo - P.pl0,
+                               lo - c * chl, acc);
+            if (S > 1)
+                hipLaunchKernelGGL(k_map_sum<R>, dim3(unsigned((map + 255) / 256)), dim3(256), 0, s,
+                                   (const R*)partial, S, corr, dirty + size_t(c) * map, int(map), acc);
         });
     } else {
         {
@@ -48,7 +60,7 @@ void launch_fft_n(bool grid, const DevParams& P, const uint32_t* mask, const uin
             segments([&](int c, int lo, int hi) {
                 DevParams Q = P;
                 Q.pln = hi - lo;
-                hipLaunchKernelGGL((k_degrid_fft_b<R, NP>), dim3(grid_b), dim3(C::kNLr * C::T), 0, s,
+                hipLaunchKernelGGL((k_degrid_fft_b<R, NP>), dim3(grid_b, parts(Q.pln)), dim3(C::kNLr * C::T), 0, s,
                                    image + size_t(c) * map, corr, tw, rows, inter, Q, lo - P.pl0, lo - c * chl);
             });
         }

@@ -475,6 +475,13 @@ int build_tables(wsg_plan* p) {
     for (int i = 0; i < ta.last_radix * ta.last_n; ++i) add((i / ta.last_n) * (i % ta.last_n), ta.F);
     for (int b = 0; b < Np / ta.F; ++b)
         for (int n = 0; n < ta.F; ++n) add(b * n, Np);
+    // and pass B's (line_table_size)
+    const int p2 = Np % 3 == 0 ? Np / 3 : Np, lg = log2_floor(p2);
+    int joined = 16;
+    for (int p = 1; p <= lg / 4; ++p, joined *= 16) {
+        const int radix = p < lg / 4 ? 16 : lg % 4 ? 1 << (lg % 4) : 0;
+        for (int i = 0; i < radix * joined; ++i) add((i / joined) * (i % joined), radix * joined);
+    }
     if ((rc = upload(&p->tw64, tw64.data(), tw64.size()))) return rc;
     if ((rc = upload(&p->tw32, tw32.data(), tw32.size()))) return rc;
 
