@@ -9,13 +9,6 @@ namespace wsg {
 
 // ---------------------------------------------------------------- utilities --
 
-template <typename T>
-__global__ void k_fill(T* __restrict__ p, size_t n, T v) {
-    size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    size_t stride = size_t(gridDim.x) * blockDim.x;
-    for (; i < n; i += stride) p[i] = v;
-}
-
 // Streaming copy for the bandwidth probe: each block walks kProbeUnroll
 // consecutive 16-byte vectors per thread per round (all loads issued before
 // the stores, non-temporal both ways), rounds strided by the whole grid.  Of
@@ -115,12 +108,17 @@ __device__ __forceinline__ int bin_of(const VisCoords& c, const DevParams& P) {
     return (c.rt / kTileT * P.nbs + c.rv / kTileS) * P.nbr + c.ru / kTileR;
 }
 
-// Bin counts and cursors are updated with device-scope atomics, whose cost is
-// per operation.  A block therefore takes a chunk of kAggChunk consecutive
-// visibilities (a run of time steps of every baseline, whose tracks stay in few
-// bins) and aggregates them per bin in an LDS table (open addressing, bounded
-// probing) before one global update per distinct bin; a visibility whose bin
-// finds no table slot updates the global counter directly.
+// Bin counts are updated with device-scope atomics, whose cost is per operation
+// and, on one address, serial.  A block of k_bin_count therefore takes a chunk of
+// kAggChunk consecutive visibilities (a run of time steps of every baseline, whose
+// tracks stay in few bins) and aggregates them per bin in an LDS table (open
+// addressing, bounded probing) before one global update per distinct bin; a
+// visibility whose bin finds no table slot updates the global counter directly.
+// Either way the counter's value and the place in the table give each visibility
+// its place in its bin (`rank`), so that the records need no second table
+// (scatter kernel, 10M visibilities: 358 -> 257 us, 16M of 128 antennas 1129 ->
+// 448).  Chunks of 1,024 make the fullest bins' counters wait for each other
+// (301,717 visibilities: 48 us against 28).
 constexpr int kAggThreads = 1024;
 constexpr int kAggPer = 8;
 constexpr int kAggChunk = kAggThreads * kAggPer;
@@ -130,27 +128,27 @@ constexpr int kAggProbes = 32;
 struct AggTable {
     int key[kAggSlots];
     uint32_t cnt[kAggSlots];
-    uint32_t base[kAggSlots];
     uint32_t skipped;
 };
 
-// Binning blocks of a batched call: block b belongs to channel c when
-// cblk[c] <= b < cblk[c + 1]; channel c's visibilities are [coff[c], coff[c + 1])
-// of the concatenated arrays, kAggChunk of them per block (one channel per
-// block, so the lookup is wave-uniform).
+// Binning blocks of a batched call: channel c's visibilities are
+// [coff[c], coff[c + 1]) of the concatenated arrays, CHUNK of them per block (one
+// channel per block, so the lookup is wave-uniform).
 struct ChunkRange {
     long long k0, k1;
     int ch;
 };
-__device__ __forceinline__ ChunkRange chunk_of_block(const long long* __restrict__ coff,
-                                                     const int* __restrict__ cblk, int nch) {
-    const int b = blockIdx.x;
-    int c = 0;
-    while (c + 1 < nch && cblk[c + 1] <= b) ++c;
+template <int CHUNK>
+__device__ __forceinline__ ChunkRange chunk_of_block(const long long* __restrict__ coff, int nch) {
     ChunkRange r;
-    r.ch = c;
-    r.k0 = coff[c] + (long long)(b - cblk[c]) * kAggChunk;
-    r.k1 = min(coff[c + 1], r.k0 + kAggChunk);
+    r.ch = 0;
+    for (long long b = blockIdx.x;; ++r.ch) {
+        r.k0 = coff[r.ch] + b * CHUNK;
+        r.k1 = coff[r.ch + 1];
+        if (r.ch + 1 >= nch || r.k0 < r.k1) break;
+        b -= (r.k1 - coff[r.ch] + CHUNK - 1) / CHUNK;
+    }
+    r.k1 = min(r.k1, r.k0 + CHUNK);
     return r;
 }
 
@@ -178,14 +176,13 @@ __device__ __forceinline__ int agg_slot(AggTable& T, int key) {
 }
 
 static __global__ void __launch_bounds__(kAggThreads) k_bin_count(const double* __restrict__ uvw,
-                                                           const long long* __restrict__ coff,
-                                                           const int* __restrict__ cblk, DevParams P,
+                                                           const long long* __restrict__ coff, DevParams P,
                                                            uint32_t* __restrict__ count,
-                                                           uint32_t* __restrict__ skipped) {
+                                                           uint32_t* __restrict__ skipped, uint32_t* __restrict__ rank) {
     __shared__ AggTable T;
     agg_init(T);
     __syncthreads();
-    const ChunkRange cr = chunk_of_block(coff, cblk, P.nch);
+    const ChunkRange cr = chunk_of_block<kAggChunk>(coff, P.nch);
     uint32_t my_skipped = 0;
     // the thread's coordinates, all loads in flight at once
     double xu[kAggPer], xv[kAggPer], xw[kAggPer];
@@ -197,10 +194,12 @@ static __global__ void __launch_bounds__(kAggThreads) k_bin_count(const double* 
         xv[i] = in ? uvw[3 * k + 1] : 0.0;
         xw[i] = in ? uvw[3 * k + 2] : 0.0;
     }
+    uint32_t tag[kAggPer];       // slot << 16 | place among the block's; 0xffffffff: rank written already
 #pragma unroll
     for (int i = 0; i < kAggPer; ++i) {
+        tag[i] = 0xffffffffu;
         const long long k = cr.k0 + (long long)i * kAggThreads + threadIdx.x;
-        if (k >= cr.k1) break;
+        if (k >= cr.k1) continue;
         VisCoords c;
         if (!vis_coords_of(xu[i], xv[i], xw[i], cr.ch, P, c)) {
             ++my_skipped;
@@ -208,20 +207,60 @@ static __global__ void __launch_bounds__(kAggThreads) k_bin_count(const double* 
         }
         const int b = bin_of(c, P);
         const int sl = agg_slot(T, b);
-        if (sl >= 0)
-            atomicAdd(&T.cnt[sl], 1u);
-        else
-            atomicAdd(&count[b], 1u);
+        if (sl >= 0) tag[i] = (uint32_t(sl) << 16) | atomicAdd(&T.cnt[sl], 1u);
+        else rank[k] = atomicAdd(&count[b], 1u);
     }
     if (my_skipped) atomicAdd(&T.skipped, my_skipped);
     __syncthreads();
     for (int i = threadIdx.x; i < kAggSlots; i += kAggThreads)
-        if (T.key[i] >= 0) atomicAdd(&count[T.key[i]], T.cnt[i]);
+        if (T.key[i] >= 0) T.cnt[i] = atomicAdd(&count[T.key[i]], T.cnt[i]);
     if (threadIdx.x == 0 && T.skipped) atomicAdd(skipped, T.skipped);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAggPer; ++i)
+        if (tag[i] != 0xffffffffu)
+            rank[cr.k0 + (long long)i * kAggThreads + threadIdx.x] = T.cnt[tag[i] >> 16] + (tag[i] & 0xffffu);
+}
+
+// Clears the counters and marks of a binning, which sit side by side in the
+// workspace, and writes the channel table (one launch for what were six).
+template <typename Args>
+__global__ void k_bin_init(Args ca, int nch, long long* __restrict__ coff, uint32_t* __restrict__ zero, size_t words) {
+    if (blockIdx.x == 0 && int(threadIdx.x) <= nch) coff[threadIdx.x] = ca.off[threadIdx.x];
+    for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < words; i += size_t(gridDim.x) * blockDim.x)
+        zero[i] = 0u;
+}
+
+// The wave's next places of a counter for its lanes with `want` (one atomic per wave).
+__device__ __forceinline__ uint32_t wave_reserve(uint32_t* counter, bool want) {
+    const unsigned long long m = __ballot(want);
+    if (m == 0) return 0u;
+    const int lane = threadIdx.x & 63, first = __builtin_ctzll(m);
+    uint32_t base = 0;
+    if (lane == first) base = atomicAdd(counter, uint32_t(__popcll(m)));
+    return __shfl(base, first, 64) + uint32_t(__popcll(m & ((1ull << lane) - 1ull)));
+}
+
+// Counts of few visibilities: a thread each, its place in its bin straight from
+// the bin's counter (5,000 visibilities: 11 -> 4 us, 46,332: 17 -> 8).  With more
+// the atomics on the fullest bins wait for each other (120,011: 34 us, 2M: 224).
+constexpr int kDirectThreads = 256;
+static __global__ void __launch_bounds__(kDirectThreads) k_bin_count_direct(const double* __restrict__ uvw,
+                                                           const long long* __restrict__ coff, DevParams P,
+                                                           uint32_t* __restrict__ count,
+                                                           uint32_t* __restrict__ skipped, uint32_t* __restrict__ rank) {
+    const ChunkRange cr = chunk_of_block<kDirectThreads>(coff, P.nch);
+    const long long k = cr.k0 + threadIdx.x;
+    VisCoords c;
+    const bool in = k < cr.k1, ok = in && vis_coords(uvw, k, cr.ch, P, c);
+    if (ok) rank[k] = atomicAdd(&count[bin_of(c, P)], 1u);
+    wave_reserve(skipped, in && !ok);
 }
 
 // Exclusive scan of n uint32 counts: per-block scan (1024 items per block of
-// 256 threads), scan of the block sums in one block, then add.
+// 256 threads), scan of the block sums in one block, then add; n up to
+// kScanSmall in one block of 1024 threads, four items each at a time (5 us at
+// 4,096 items, 22 at 32,768; the three launches 14 us up to there).
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* sh, uint32_t& total) {
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     uint32_t inc = x;
@@ -261,6 +300,31 @@ static __global__ void k_scan_local(const uint32_t* __restrict__ in, uint32_t* _
     if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
 }
 
+constexpr int kScanSmall = 8192;
+static __global__ void __launch_bounds__(1024) k_scan_small(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
+                                                            int n, uint32_t* __restrict__ grand) {
+    __shared__ uint32_t sh[16];
+    uint32_t carry = 0;
+    for (int i0 = 0; i0 < n; i0 += 4096) {
+        const int base = i0 + threadIdx.x * 4;
+        uint32_t v[4], s = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = (base + i < n) ? in[base + i] : 0u;
+            s += v[i];
+        }
+        uint32_t total;
+        uint32_t off = carry + block_exclusive_scan(s, sh, total);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (base + i < n) out[base + i] = off;
+            off += v[i];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) *grand = carry;
+}
+
 // single block of 1024 threads; each thread scans ceil(nb / 1024) consecutive sums
 static __global__ void k_scan_sums(uint32_t* __restrict__ block_sums, int nb, uint32_t* __restrict__ grand) {
     __shared__ uint32_t sh[16];
@@ -289,78 +353,54 @@ static __global__ void k_scan_add(uint32_t* __restrict__ out, int n, const uint3
         if (base + i < n) out[base + i] += add;
 }
 
+// The record of visibility k.
 // grid: v = V exp(+i 2 pi w (n0 - 1)) with n0 - 1 = -zshift n_scale (eq. n_params:
 // zshift = z0; zero without z offset, eq. n_params_no_offset),
 // V conjugated for a folded visibility.  degrid: v = exp(-i 2 pi w (n0 - 1)).
 template <typename R, bool GRID>
-__global__ void __launch_bounds__(kAggThreads) k_bin_scatter(const double* __restrict__ uvw,
+__device__ __forceinline__ Rec<R> make_rec(const VisCoords& c, long long k, const cpx<R>* __restrict__ vis,
+                                           const DevParams& P) {
+    Rec<R> r;
+    r.ruv = uint32_t(c.ru) | (uint32_t(c.rv) << 16);
+    r.rt = uint32_t(c.rt);
+    r.nu[0] = R(c.nu_u);
+    r.nu[1] = R(c.nu_v);
+    r.nu[2] = R(c.nu_w);
+    double turns = c.w * (-P.zshift * P.nscale);     // w (n0 - 1)
+    double sn, co;
+    phase_turns(GRID ? turns : -turns, &sn, &co);
+    if (GRID) {
+        cpx<R> V = vis[k];
+        double vx = double(V.x), vy = c.folded ? -double(V.y) : double(V.y);
+        r.v[0] = R(vx * co - vy * sn);
+        r.v[1] = R(vx * sn + vy * co);
+        r.idx = 0;
+    } else {
+        r.v[0] = R(co);
+        r.v[1] = R(sn);
+        r.idx = uint32_t(k) | (c.folded ? 0x80000000u : 0u);
+    }
+    return r;
+}
+
+// The records, binned.  degrid: a skipped visibility leaves its index behind the
+// last record (counted down from the end of `tail`), for k_degrid_finish.
+template <typename R, bool GRID>
+__global__ void __launch_bounds__(kDirectThreads) k_bin_scatter(const double* __restrict__ uvw,
                                                              const cpx<R>* __restrict__ vis,
-                                                             const long long* __restrict__ coff,
-                                                             const int* __restrict__ cblk, DevParams P,
+                                                             const long long* __restrict__ coff, DevParams P,
                                                              const uint32_t* __restrict__ start,
-                                                             uint32_t* __restrict__ cursor, Rec<R>* __restrict__ rec) {
-    __shared__ AggTable T;
-    agg_init(T);
-    __syncthreads();
-    const ChunkRange cr = chunk_of_block(coff, cblk, P.nch);
-    const long long k0 = cr.k0;
-    // the thread's coordinates, loaded once for both passes, all in flight at once
-    double xu[kAggPer], xv[kAggPer], xw[kAggPer];
-#pragma unroll
-    for (int i = 0; i < kAggPer; ++i) {
-        const long long k = k0 + (long long)i * kAggThreads + threadIdx.x;
-        const bool in = k < cr.k1;
-        xu[i] = in ? uvw[3 * k] : 0.0;
-        xv[i] = in ? uvw[3 * k + 1] : 0.0;
-        xw[i] = in ? uvw[3 * k + 2] : 0.0;
-    }
-    // pass 1: rank of each visibility among this block's visibilities of its bin
-    uint32_t tag[kAggPer];             // slot << 16 | rank; 0xffffffff: direct update
-#pragma unroll
-    for (int i = 0; i < kAggPer; ++i) {
-        tag[i] = 0xffffffffu;
-        const long long k = k0 + (long long)i * kAggThreads + threadIdx.x;
-        VisCoords c;
-        if (k < cr.k1 && vis_coords_of(xu[i], xv[i], xw[i], cr.ch, P, c)) {
-            const int sl = agg_slot(T, bin_of(c, P));
-            if (sl >= 0) tag[i] = (uint32_t(sl) << 16) | atomicAdd(&T.cnt[sl], 1u);
-        }
-    }
-    __syncthreads();
-    // one reservation per distinct bin of the block
-    for (int i = threadIdx.x; i < kAggSlots; i += kAggThreads)
-        if (T.key[i] >= 0) T.base[i] = atomicAdd(&cursor[T.key[i]], T.cnt[i]);
-    __syncthreads();
-    // pass 2: write the records
-#pragma unroll
-    for (int i = 0; i < kAggPer; ++i) {
-        const long long k = k0 + (long long)i * kAggThreads + threadIdx.x;
-        VisCoords c;
-        if (!(k < cr.k1 && vis_coords_of(xu[i], xv[i], xw[i], cr.ch, P, c))) continue;
-        const int b = bin_of(c, P);
-        const uint32_t off = tag[i] != 0xffffffffu ? T.base[tag[i] >> 16] + (tag[i] & 0xffffu)
-                                                   : atomicAdd(&cursor[b], 1u);
-        Rec<R> r;
-        r.ruv = uint32_t(c.ru) | (uint32_t(c.rv) << 16);
-        r.rt = uint32_t(c.rt);
-        r.nu[0] = R(c.nu_u);
-        r.nu[1] = R(c.nu_v);
-        r.nu[2] = R(c.nu_w);
-        double turns = c.w * (-P.zshift * P.nscale);     // w (n0 - 1)
-        double sn, co;
-        phase_turns(GRID ? turns : -turns, &sn, &co);
-        if (GRID) {
-            cpx<R> V = vis[k];
-            double vx = double(V.x), vy = c.folded ? -double(V.y) : double(V.y);
-            r.v[0] = R(vx * co - vy * sn);
-            r.v[1] = R(vx * sn + vy * co);
-            r.idx = 0;
-        } else {
-            r.v[0] = R(co);
-            r.v[1] = R(sn);
-            r.idx = uint32_t(k) | (c.folded ? 0x80000000u : 0u);
-        }
-        rec[start[b] + off] = r;
+                                                             const uint32_t* __restrict__ rank,
+                                                             uint32_t* __restrict__ spare, Rec<R>* __restrict__ rec,
+                                                             Rec<R>* __restrict__ tail) {
+    const ChunkRange cr = chunk_of_block<kDirectThreads>(coff, P.nch);
+    const long long k = cr.k0 + threadIdx.x;
+    VisCoords c;
+    const bool in = k < cr.k1, ok = in && vis_coords(uvw, k, cr.ch, P, c);
+    if (ok) rec[start[bin_of(c, P)] + rank[k]] = make_rec<R, GRID>(c, k, vis, P);
+    if constexpr (!GRID) {
+        const uint32_t at = wave_reserve(spare, in && !ok);
+        if (in && !ok) tail[coff[P.nch] - 1 - at].idx = uint32_t(k);
     }
 }
 
@@ -1598,13 +1638,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // Sum of each record's parts over the tiles it reaches (slot m is written by
 // the tile one step forward along the axes of m, present when the record's
 // touch class contains m), times the phase exp(-i 2 pi w (n0 - 1)), conjugated
-// for a folded visibility, stored to its visibility.
+// for a folded visibility, stored to its visibility.  The M - n_rec skipped
+// visibilities, whose indices follow the records, are zero.
 template <typename R>
 __global__ void k_degrid_finish(const Rec<R>* __restrict__ rec, const uint32_t* __restrict__ n_rec,
-                                const cpx<R>* __restrict__ part, size_t part_stride, int W, int Wz,
+                                const cpx<R>* __restrict__ part, size_t part_stride, size_t M, int W, int Wz,
                                 cpx<R>* __restrict__ vis) {
     const size_t p = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (p >= *n_rec) return;
+    if (p >= M) return;
+    if (p >= *n_rec) {
+        vis[rec[p].idx] = cpx<R>{R(0), R(0)};
+        return;
+    }
     const Rec<R> r = rec[p];
     const int c = class_of(int(r.rt) & (kTileT - 1), int(r.ruv & 0xffffu) & (kTileR - 1),
                            int(r.ruv >> 16) & (kTileS - 1), 17 - Wz, 17 - W);

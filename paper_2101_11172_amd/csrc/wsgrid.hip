@@ -139,7 +139,7 @@ struct wsg_plan {
 namespace {
 
 struct Layout {
-    size_t stack, inter, rec, rec2, part, count, start, cursor, bsums, cls, occ, rows, mask, chan, tpos, tlist, skipped,
+    size_t stack, inter, rec, rec2, part, count, start, bsums, cls, occ, rows, mask, cleared, chan, tpos, tlist, skipped,
         total;
     int nch, nbins, nscan;
     int last_layer;    // end of the last channel's layers on the virtual layer axis
@@ -148,11 +148,10 @@ struct Layout {
 
 constexpr int kMaxChannels = 64;
 
-// Channel table of a batched call, copied to the workspace by one tiny kernel:
-// visibility offsets and first binning block of each channel.
+// Channel table of a batched call, copied to the workspace when a binning begins:
+// visibility offset of each channel.
 struct ChanArgs {
     long long off[kMaxChannels + 1];
-    int blk[kMaxChannels + 1];
 };
 
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -170,20 +169,21 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     const size_t Np = size_t(p->pp.Nprime), nl = size_t(L.pass_layers);
     L.nbins = nch * p->nbins();
     L.nscan = (L.nbins + 1023) / 1024;
-    // the skipped counter sits at offset 0 whatever M and the precision
+    // the skipped counter sits at offset 0 whatever M and the precision (the next
+    // word counts the skipped indices behind the records); what a binning clears comes first
     size_t off = 0;
     L.skipped = off; off += 256;
     L.count = off;   off += al256(size_t(L.nbins) * 4);
+    L.rows = off;    off += al256(size_t(nch) * p->nbt * p->nbr);
+    L.mask = off;    off += al256(size_t(nch) * p->nbt * p->nbr * mask_words(p->nbs) * 4);
+    L.cleared = off;
     L.start = off;   off += al256(size_t(L.nbins + 1) * 4);
-    L.cursor = off;  off += al256(size_t(L.nbins) * 4);
     L.bsums = off;   off += al256(size_t(L.nscan) * 4);
     L.cls = off;     off += al256(size_t(L.nbins) * 8 * 4);
     L.occ = off;     off += al256(size_t(L.nbins));
-    L.rows = off;    off += al256(size_t(nch) * p->nbt * p->nbr);
-    L.mask = off;    off += al256(size_t(nch) * p->nbt * p->nbr * mask_words(p->nbs) * 4);
     L.tpos = off;    off += al256(size_t(L.nbins + 1) * 4);
     L.tlist = off;   off += al256(std::min(size_t(L.nbins), 8 * size_t(M)) * sizeof(TileRec));   // a record reaches 8 tiles at most
-    L.chan = off;    off += al256(sizeof(long long) * (kMaxChannels + 1)) + al256(sizeof(int) * (kMaxChannels + 1));
+    L.chan = off;    off += al256(sizeof(long long) * (kMaxChannels + 1));
     // the large buffers start on 2 MiB boundaries (their power-of-two line
     // strides then meet the memory channels the same way whatever precedes them)
     off = al2m(off);
@@ -222,27 +222,19 @@ DevParams dev_params(const wsg_plan* p) {
     return P;
 }
 
-template <typename T>
-void fill(T* ptr, size_t n, T v, hipStream_t s) {
-    if (n == 0) return;
-    size_t blocks = std::min<size_t>((n + 255) / 256, 65536);
-    hipLaunchKernelGGL(k_fill<T>, dim3(unsigned(blocks)), dim3(256), 0, s, ptr, n, v);
-}
-
 void scan(const uint32_t* count, uint32_t* start, uint32_t* bsums, int n, hipStream_t s) {
+    if (n <= kScanSmall) {
+        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, count, start, n, start + n);
+        return;
+    }
     const int nb = (n + 1023) / 1024;
     hipLaunchKernelGGL(k_scan_local, dim3(nb), dim3(256), 0, s, count, start, n, bsums);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, bsums, nb, start + n);
     hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(256), 0, s, start, n, (const uint32_t*)bsums);
 }
 
-__global__ void k_set_chan(ChanArgs ca, int nch, long long* __restrict__ coff, int* __restrict__ cblk) {
-    const int i = threadIdx.x;
-    if (i <= nch) {
-        coff[i] = ca.off[i];
-        cblk[i] = ca.blk[i];
-    }
-}
+// Visibilities up to which the count takes a thread each (k_bin_count_direct).
+constexpr int64_t kDirectMost = 1 << 16;
 
 // a: the input array, b: the output array; with M = 0 the visibility-sized
 // one of them may be null (nothing is read from or written to it).  Mc: the
@@ -292,7 +284,6 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
     auto* rec = reinterpret_cast<Rec<R>*>(w + L.rec);        // binned and sorted within each bin
     auto* count = reinterpret_cast<uint32_t*>(w + L.count);
     auto* start = reinterpret_cast<uint32_t*>(w + L.start);
-    auto* cursor = reinterpret_cast<uint32_t*>(w + L.cursor);
     auto* bsums = reinterpret_cast<uint32_t*>(w + L.bsums);
     auto* cls = reinterpret_cast<uint32_t*>(w + L.cls);
     auto* occ = reinterpret_cast<uint8_t*>(w + L.occ);
@@ -301,40 +292,43 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
     auto* tpos = reinterpret_cast<uint32_t*>(w + L.tpos);
     auto* tlist = reinterpret_cast<TileRec*>(w + L.tlist);
     auto* coff = reinterpret_cast<long long*>(w + L.chan);
-    auto* cblk = reinterpret_cast<int*>(w + L.chan + al256(sizeof(long long) * (kMaxChannels + 1)));
     auto* skipped = reinterpret_cast<uint32_t*>(w + L.skipped);
 
-    // channel table: visibility offsets and binning blocks (one channel per block)
+    // channel table, and how many blocks of `chunk` visibilities of one channel there are
     ChanArgs ca{};
-    for (int c = 0; c < L.nch; ++c) {
-        ca.off[c + 1] = ca.off[c] + Mc[c];
-        ca.blk[c + 1] = ca.blk[c] + int((Mc[c] + kAggChunk - 1) / kAggChunk);
-    }
-    const unsigned vblocks = unsigned(ca.blk[L.nch]);
+    for (int c = 0; c < L.nch; ++c) ca.off[c + 1] = ca.off[c] + Mc[c];
+    auto blocks = [&](int chunk) {
+        int64_t n = 0;
+        for (int c = 0; c < L.nch; ++c) n += (Mc[c] + chunk - 1) / chunk;
+        return dim3(unsigned(n));
+    };
+    const int64_t M = ca.off[L.nch];
+    auto* rank = reinterpret_cast<uint32_t*>(w + L.part);     // free until the gather
+    auto* vis = static_cast<const cpx<R>*>(in);
     {
         StageMark mark(s, stage);
-        hipLaunchKernelGGL(k_set_chan, dim3(1), dim3(128), 0, s, ca, L.nch, coff, cblk);
-        fill<uint32_t>(count, size_t(L.nbins), 0u, s);
-        fill<uint32_t>(cursor, size_t(L.nbins), 0u, s);
-        fill<uint32_t>(skipped, 1, 0u, s);
-        if (vblocks > 0)
-            hipLaunchKernelGGL(k_bin_count, dim3(vblocks), dim3(kAggThreads), 0, s, uvw, (const long long*)coff,
-                               (const int*)cblk, P, count, skipped);
+        const size_t words = L.cleared / 4;
+        hipLaunchKernelGGL(k_bin_init<ChanArgs>, dim3(unsigned(std::min<size_t>((words + 255) / 256, 2048))), dim3(256),
+                           0, s, ca, L.nch, coff, reinterpret_cast<uint32_t*>(w), words);
+        if (M > kDirectMost)
+            hipLaunchKernelGGL(k_bin_count, blocks(kAggChunk), dim3(kAggThreads), 0, s, uvw, (const long long*)coff, P,
+                               count, skipped, rank);
+        else if (M > 0)
+            hipLaunchKernelGGL(k_bin_count_direct, blocks(kDirectThreads), dim3(kDirectThreads), 0, s, uvw,
+                               (const long long*)coff, P, count, skipped, rank);
         scan(count, start, bsums, L.nbins, s);
-        if (vblocks > 0) {
+        if (M > 0) {
             if (grid)
-                hipLaunchKernelGGL((k_bin_scatter<R, true>), dim3(vblocks), dim3(kAggThreads), 0, s, uvw,
-                                   static_cast<const cpx<R>*>(in), (const long long*)coff, (const int*)cblk, P,
-                                   (const uint32_t*)start, cursor, rec_bin);
+                hipLaunchKernelGGL((k_bin_scatter<R, true>), blocks(kDirectThreads), dim3(kDirectThreads), 0, s, uvw, vis,
+                                   (const long long*)coff, P, (const uint32_t*)start, (const uint32_t*)rank, skipped + 1,
+                                   rec_bin, rec);
             else
-                hipLaunchKernelGGL((k_bin_scatter<R, false>), dim3(vblocks), dim3(kAggThreads), 0, s, uvw,
-                                   (const cpx<R>*)nullptr, (const long long*)coff, (const int*)cblk, P,
-                                   (const uint32_t*)start, cursor, rec_bin);
+                hipLaunchKernelGGL((k_bin_scatter<R, false>), blocks(kDirectThreads), dim3(kDirectThreads), 0, s, uvw,
+                                   vis, (const long long*)coff, P, (const uint32_t*)start, (const uint32_t*)rank,
+                                   skipped + 1, rec_bin, rec);
             hipLaunchKernelGGL(k_bin_local_sort<R>, dim3(L.nbins), dim3(256), 0, s, (const Rec<R>*)rec_bin, rec,
                                (const uint32_t*)start, cls, P);
         }
-        fill<uint8_t>(rows, size_t(L.nch) * P.nbt * P.nbr, uint8_t(0), s);
-        fill<uint32_t>(mask, size_t(L.nch) * P.nbt * P.nbr * mask_words(P.nbs), 0u, s);
         // occupancy marks, then the ordered list of occupied tiles (the bin
         // counts are no longer needed: they take the 32-bit marks for the scan)
         hipLaunchKernelGGL(k_tile_occupancy, dim3((L.nbins + 255) / 256), dim3(256), 0, s, (const uint32_t*)start,
@@ -397,12 +391,11 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
         }
     }
     if (!grid) {
-        fill<R>(static_cast<R*>(out), size_t(2 * M), R(0), s);     // skipped visibilities stay zero
         StageMark mark(s, 7);
         if (M > 0)
             hipLaunchKernelGGL(k_degrid_finish<R>, dim3(unsigned((M + 255) / 256)), dim3(256), 0, s,
                                (const Rec<R>*)rec, (const uint32_t*)(start + L.nbins), (const cpx<R>*)part,
-                               size_t(M), P.W, P.Wz, static_cast<cpx<R>*>(out));
+                               size_t(M), size_t(M), P.W, P.Wz, static_cast<cpx<R>*>(out));
     }
     WSG_HIP(hipGetLastError());
     return WSG_OK;
