@@ -1709,7 +1709,7 @@ __device__ __forceinline__ int shift_half(int f, int half) {
 // Bound by latency and VALU issue (about half of the issue slots are used, two
 // blocks of 8 waves per CU).  Wide field (N' = 4096, 49 layers, one pass), with
 // the transpose of the intermediate that a whole-line pass needs: FP32 grid
-// 2.13 -> 1.76 ms, degrid 2.06 -> 2.00; FP64 4.55 -> 3.49 and 4.58 -> 3.71;
+// 2.13 -> 1.56 ms, degrid 2.06 -> 2.00; FP64 4.55 -> 2.96 and 4.58 -> 3.71;
 // N' = 3072 FP32 degrid 1.63 -> 0.97.  Rows are dealt to the XCDs in turn: the
 // marked rows thin out towards the upper layers, and with a contiguous range of
 // rows per XCD the grid direction took 2.90 ms.  At kRows = 16 (one block of
@@ -1735,13 +1735,17 @@ struct PassACfg {
 // image rows q kept, written to the intermediate.  The marked tiles of the row
 // (about a fifth of them at wide field) are listed and only they are read; a row
 // of tiles with none marked is neither transformed nor written (pass B reads it
-// as zeros).  Layer t of the pass is virtual layer t + t_base; in a batched call
+// as zeros).  A block takes `each` layers of a tile layer, whose marks they
+// share, and loads the next one's cells while it transforms (a layer per block:
+// 1.76 ms at wide field, FP64 3.49; 16 cells instead of 8 in flight spill: 1.66).
+// Layer t of the pass is virtual layer t + t_base; in a batched call
 // (chl = the channels' layer stride, else 0) a padding layer (virtual layer mod
 // chl >= n_layers) is skipped.
 template <typename R, int NP>
 __global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((amdgpu_waves_per_eu(PassACfg<R, NP>::kWaves)))
     k_grid_fft_a(const cpx<R>* __restrict__ stack, const uint32_t* __restrict__ mask, cpx<R>* __restrict__ inter,
-                 const cpx<R>* __restrict__ tw, int N, int n_layers, int chl, int nbr, int t_base) {
+                 const cpx<R>* __restrict__ tw, int N, int n_layers, int chl, int nbr, int t_base, int pln,
+                 int each) {
     using A = PassACfg<R, NP>;
     constexpr int C = A::kClasses, F = A::F, T = A::T, RW = A::kRows, LP = A::LP, NB = NP / kTileS, TH = A::kThreads;
     constexpr int MW = mask_words(NB), PART = RW * kTileS;       // cells of a tile in the block
@@ -1756,14 +1760,18 @@ __global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((am
     constexpr bool TURNS = sizeof(R) == 4 || G * EG <= 384;
     __shared__ cpx<R> tile_turn[TURNS ? G * EG : 1];
     __shared__ int count[G];
+    __shared__ uint32_t empty[G];        // bit k: no marked tile among the parts of n / 16 = k G + group
     int lb = xcd_interleave<A::kHalves * C>(blockIdx.x, gridDim.x);
     const int b = lb % C;
     lb /= C;
     const int h = lb % A::kHalves;
     lb /= A::kHalves;
-    const int rt = lb % nbr, t = lb / nbr;
-    if (chl > 0 && (t + t_base) % chl >= n_layers) return;     // padding layer of a channel (block-uniform)
-    const uint32_t* mrow = mask + size_t(((t + t_base) / kTileT) * nbr + rt) * MW;     // the row's marked tiles
+    // the block's layers, of one tile layer; padding layers of a channel (at a tile layer's end) left out
+    const int rt = lb % nbr, first = lb / nbr * each;
+    int end = min(pln, first + each);
+    if (chl > 0) end = min(end, first + max(0, n_layers - (first + t_base) % chl));
+    if (first >= end) return;
+    const uint32_t* mrow = mask + size_t(((first + t_base) / kTileT) * nbr + rt) * MW;     // the row's marked tiles
     uint32_t any = 0;
 #pragma unroll
     for (int i = 0; i < MW; ++i) any |= mrow[i];
@@ -1775,6 +1783,7 @@ __global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((am
         const int lane = tid & 63, w = tid >> 6;
         if (w < G) {
             int n = 0;
+            uint32_t none = 0;
             for (int i0 = 0; i0 < EG; i0 += STEP) {
                 const int i = i0 + lane, m = i % C, bs = i / C * G + w + m * (F / kTileS);
                 const bool on = lane < STEP && i < EG && ((mrow[bs >> 5] >> (bs & 31)) & 1u);
@@ -1785,95 +1794,116 @@ __global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((am
                     list[at] = uint16_t(bs | (last ? 0x8000 : 0));
                     if constexpr (TURNS) tile_turn[at] = tw[bs * kTileS * b % NP];
                 }
+                const uint64_t here = (all >> lane) & ((1ull << C) - 1ull);
+                none |= lane < STEP && i < EG && m == 0 && here == 0ull ? 1u << (i / C) : 0u;
                 n += __popcll(all);
             }
-            if (lane == 0) count[w] = n;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) none |= uint32_t(__shfl_xor(int(none), o, 64));
+            if (lane == 0) {
+                count[w] = n;
+                empty[w] = none;
+            }
         }
     }
     for (int i = tid; i < TB.second; i += TH) tab[i] = tw[NP + i];
-    for (int i = tid; i < RW * LP; i += TH) buf[i] = cpx<R>{R(0), R(0)};
     __syncthreads();
-    // buf[r][n] = sum_m x[n + F m] W_N'^((n + F m) b): each cell of the marked
-    // tiles is read once, kBatch tiles in flight per thread; W_N'^(s b) is the
-    // tile's W_N'^(16 bs b) (wave-uniform) times the cell's W_N'^((s mod 16) b)
-    {
+    const int g = G > 1 ? __builtin_amdgcn_readfirstlane(tid / PART) : 0, e0 = tid % PART;
+    const int n_list = __builtin_amdgcn_readfirstlane(count[g]);
+    const uint32_t none = uint32_t(__builtin_amdgcn_readfirstlane(int(empty[g])));
+    constexpr int kBatch = (8 + Q - 1) / Q;
+    cpx<R> turn[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) turn[q] = tw[(e0 + q * TH) % kTileS * b];
+    cpx<R> x[kBatch][Q];
+    auto load = [&](int t, int base) {
         const cpx<R>* src = stack + (size_t(t) * nbr + rt) * (size_t(NB) * kTileR * kTileS) + h * PART;
-        const int g = G > 1 ? __builtin_amdgcn_readfirstlane(tid / PART) : 0, e0 = tid % PART;
-        const int n_list = __builtin_amdgcn_readfirstlane(count[g]);
-        constexpr int kBatch = 16 / Q;
-        cpx<R> acc[Q], turn[Q];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            acc[q] = cpx<R>{R(0), R(0)};
-            turn[q] = tw[(e0 + q * TH) % kTileS * b];
-        }
-        for (int base = 0; base < n_list; base += kBatch) {
-            cpx<R> x[kBatch][Q];
-            int en[kBatch];
+        for (int u = 0; u < kBatch; ++u)
+            if (base + u < n_list) {
+                const int bs = __builtin_amdgcn_readfirstlane(int(list[g * EG + base + u])) & 0x7fff;
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                en[u] = base + u < n_list ? __builtin_amdgcn_readfirstlane(int(list[g * EG + base + u])) : -1;
-                if (en[u] >= 0) {
-#pragma unroll
-                    for (int q = 0; q < Q; ++q)
-                        x[u][q] = src[size_t(en[u] & 0x7fff) * (kTileR * kTileS) + (e0 + q * TH)];
-                }
+                for (int q = 0; q < Q; ++q) x[u][q] = src[size_t(bs) * (kTileR * kTileS) + (e0 + q * TH)];
             }
+    };
+    load(first, 0);
+    const int half = N / 2;
+    for (int t = first; t < end; ++t) {
+        // buf[r][n] = sum_m x[n + F m] W_N'^((n + F m) b): each cell of the marked
+        // tiles is read once, kBatch tiles in flight per thread (the next layer's
+        // first ones during this layer's transform); W_N'^(s b) is the tile's
+        // W_N'^(16 bs b) (wave-uniform) times the cell's W_N'^((s mod 16) b).  A
+        // group's threads write every n of theirs.
+        if (t > first) __syncthreads();
+        for (uint32_t z = none; z; z &= z - 1) {
+            const int n16 = __builtin_ctz(z) * G + g;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int e = e0 + q * TH;
+                buf[e / kTileS * LP + lpad(n16 * kTileS + e % kTileS)] = cpx<R>{R(0), R(0)};
+            }
+        }
+        cpx<R> acc[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) acc[q] = cpx<R>{R(0), R(0)};
+        for (int base = 0; base < n_list; base += kBatch) {
+            if (base > 0) load(t, base);
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                if (en[u] < 0) break;
-                const int bs = en[u] & 0x7fff;
-                const cpx<R> w = TURNS ? tile_turn[g * EG + base + u] : tw[bs * kTileS * b % NP];
+                if (base + u < n_list) {
+                    const int en = __builtin_amdgcn_readfirstlane(int(list[g * EG + base + u])), bs = en & 0x7fff;
+                    const cpx<R> w = TURNS ? tile_turn[g * EG + base + u] : tw[bs * kTileS * b % NP];
 #pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    acc[q].x += x[u][q].x * w.x - x[u][q].y * w.y;
-                    acc[q].y += x[u][q].x * w.y + x[u][q].y * w.x;
-                    if (en[u] & 0x8000) {
-                        const int e = e0 + q * TH, n = (bs * kTileS + e % kTileS) & (F - 1);
-                        buf[e / kTileS * LP + lpad(n)] = cmul(acc[q], turn[q]);
-                        acc[q] = cpx<R>{R(0), R(0)};
+                    for (int q = 0; q < Q; ++q) {
+                        acc[q].x += x[u][q].x * w.x - x[u][q].y * w.y;
+                        acc[q].y += x[u][q].x * w.y + x[u][q].y * w.x;
+                        if (en & 0x8000) {
+                            const int e = e0 + q * TH, n = (bs * kTileS + e % kTileS) & (F - 1);
+                            buf[e / kTileS * LP + lpad(n)] = cmul(acc[q], turn[q]);
+                            acc[q] = cpx<R>{R(0), R(0)};
+                        }
                     }
                 }
             }
         }
-    }
-    __syncthreads();
-    cpx<R>* lbuf = buf + line * LP;
-    const int pj = lpad(j);
-    cpx<R> v[16];
+        if (t + 1 < end) load(t + 1, 0);
+        __syncthreads();
+        cpx<R>* lbuf = buf + line * LP;
+        const int pj = lpad(j);
+        cpx<R> v[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = lbuf[lpad_at<T>(j, pj, k)];
-    fft_wave<R, F, +1>(v, lbuf, tab, tw + NP + TB.second, j);
-    // class output a is bin f = C a + b, image row (f + N/2) mod N': the kept
-    // ones are a < a0 (image rows from N/2) and a >= a1 (image rows below N/2)
-    const int half = N / 2;
-    const int a0 = (N - half - b + C - 1) / C, a1 = (NP - half - b + C - 1) / C;
-    wave_sync();
+        for (int k = 0; k < 16; ++k) v[k] = lbuf[lpad_at<T>(j, pj, k)];
+        fft_wave<R, F, +1>(v, lbuf, tab, tw + NP + TB.second, j);
+        // class output a is bin f = C a + b, image row (f + N/2) mod N': the kept
+        // ones are a < a0 (image rows from N/2) and a >= a1 (image rows below N/2)
+        const int a0 = (N - half - b + C - 1) / C, a1 = (NP - half - b + C - 1) / C;
+        wave_sync();
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int a = j + T * k;
-        if (a < a0 || a >= a1) lbuf[lpad_at<T>(j, pj, k)] = v[k];
-    }
-    __syncthreads();
-    // lanes over r; step T classes outputs = C T image rows
-    const int r = tid % RW, i0 = tid / RW;
-    cpx<R>* dst = inter + (size_t(t) * inter_blocks(N) * nbr + rt) * 256 + h * RW;          // block-uniform
-    auto put = [&](int a, int hi, int q0) {       // outputs a, a + T, ... < hi; a = 0 is image row q0
-        const cpx<R>* from = buf + r * LP;
-        if constexpr (C * T % 16 == 0 && T % 16 == 0) {
-            const int q = q0 + C * a;
-            uint32_t to = uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r);
-            from += lpad(a);
-            for (; a < hi; a += T, to += uint32_t(C * T / 16) * uint32_t(nbr * 256), from += T + T / 16) dst[to] = *from;
-        } else {
-            for (; a < hi; a += T) {
-                const int q = q0 + C * a;
-                dst[uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r)] = from[lpad(a)];
-            }
+        for (int k = 0; k < 16; ++k) {
+            const int a = j + T * k;
+            if (a < a0 || a >= a1) lbuf[lpad_at<T>(j, pj, k)] = v[k];
         }
-    };
-    put(i0, min(a0, F), b + half);
-    if (a1 < F) put(a1 + i0, F, b + half - NP);
+        __syncthreads();
+        // lanes over r; step T classes outputs = C T image rows
+        const int r = tid % RW, i0 = tid / RW;
+        cpx<R>* dst = inter + (size_t(t) * inter_blocks(N) * nbr + rt) * 256 + h * RW;          // block-uniform
+        auto put = [&](int a, int hi, int q0) {       // outputs a, a + T, ... < hi; a = 0 is image row q0
+            const cpx<R>* from = buf + r * LP;
+            if constexpr (C * T % 16 == 0 && T % 16 == 0) {
+                const int q = q0 + C * a;
+                uint32_t to = uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r);
+                from += lpad(a);
+                for (; a < hi; a += T, to += uint32_t(C * T / 16) * uint32_t(nbr * 256), from += T + T / 16) dst[to] = *from;
+            } else {
+                for (; a < hi; a += T) {
+                    const int q = q0 + C * a;
+                    dst[uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r)] = from[lpad(a)];
+                }
+            }
+        };
+        put(i0, min(a0, F), b + half);
+        if (a1 < F) put(a1 + i0, F, b + half - NP);
+    }
 }
 
 // Offset of frequency r within a row q of the intermediate.

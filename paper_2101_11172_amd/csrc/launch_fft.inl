@@ -38,8 +38,13 @@ void launch_fft_n(bool grid, const DevParams& P, const uint32_t* mask, const uin
     if (grid) {
         {
             StageMark mark(s, 2);
-            hipLaunchKernelGGL((k_grid_fft_a<R, NP>), dim3(grid_a), dim3(A::kThreads), 0, s, (const cpx<R>*)stack,
-                               mask, inter, tw, P.N, P.n_layers, P.nch > 1 ? chl : 0, P.nbr, P.pl0);
+            // layers of a tile layer that a block takes one after the other, as long as eight
+            // rounds of blocks are left
+            int each = kTileT;
+            while (each > 1 && grid_a / unsigned(each) < 4096u) each /= 2;
+            hipLaunchKernelGGL((k_grid_fft_a<R, NP>), dim3(grid_a / unsigned(P.pln) * unsigned((P.pln + each - 1) / each)),
+                               dim3(A::kThreads), 0, s, (const cpx<R>*)stack, mask, inter, tw, P.N, P.n_layers,
+                               P.nch > 1 ? chl : 0, P.nbr, P.pl0, P.pln, each);
         }
         StageMark mark(s, 3);
         segments([&](int c, int lo, int hi) {
