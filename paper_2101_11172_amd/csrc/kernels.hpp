@@ -1726,6 +1726,10 @@ struct PassACfg {
     static constexpr int kThreads = kRows * T;
     static constexpr int kWaves = kThreads < kMost ? 1 : sizeof(R) == 8 ? 2 : 4;     // per SIMD, as two full blocks hold
     static_assert(T <= 64 && 64 % T == 0 && (F & (F - 1)) == 0, "a line's lanes lie in one wave");
+    // degrid blocks that take several layers: at N' = 2048, 3072 and 4096 (one layer each: 2.00 ->
+    // 1.83 ms at wide field, FP64 3.81 -> 3.43); with the loop's registers N' = 8192 (8 classes)
+    // and the shorter transforms took 2-6 % longer
+    static constexpr bool kDegridLoop = F == 1024 && kClasses >= 2 && kClasses <= 4;
     // line stride in LDS: the transposed accesses of kRows lines meet distinct banks
     static constexpr int kBanks = 256 / int(sizeof(cpx<R>));
     static constexpr int LP = (LinePad<F>::size + kBanks - 1) / kBanks * kBanks + (kBanks >= kRows ? kBanks / kRows : 1);
@@ -2089,7 +2093,8 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
 template <typename R, int NP>
 __global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((amdgpu_waves_per_eu(PassACfg<R, NP>::kWaves)))
     k_degrid_fft_a(const cpx<R>* __restrict__ inter, const uint32_t* __restrict__ mask, const cpx<R>* __restrict__ tw,
-                   cpx<R>* __restrict__ stack, int N, int n_layers, int chl, int nbr, int t_base) {
+                   cpx<R>* __restrict__ stack, int N, int n_layers, int chl, int nbr, int t_base, int pln,
+                   int each) {
     using A = PassACfg<R, NP>;
     constexpr int C = A::kClasses, F = A::F, T = A::T, RW = A::kRows, LP = A::LP, NB = NP / kTileS;
     constexpr int MW = mask_words(NB), TE = kTileR * kTileS;
@@ -2101,83 +2106,95 @@ __global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((am
     lb /= C;
     const int h = lb % A::kHalves;
     lb /= A::kHalves;
-    const int rt = lb % nbr, t = lb / nbr;
-    if (chl > 0 && (t + t_base) % chl >= n_layers) return;     // padding layer of a channel (block-uniform)
-    const uint32_t* mrow = mask + size_t(((t + t_base) / kTileT) * nbr + rt) * MW;
+    // the block's layers, as for k_grid_fft_a (or one)
+    if constexpr (!A::kDegridLoop) each = 1;
+    const int rt = lb % nbr, first = lb / nbr * each;
+    int end = min(pln, first + each);
+    if (chl > 0) end = min(end, first + max(0, n_layers - (first + t_base) % chl));
+    if (first >= end) return;
+    if constexpr (!A::kDegridLoop) end = first + 1;
+    const uint32_t* mrow = mask + size_t(((first + t_base) / kTileT) * nbr + rt) * MW;
     uint32_t mw[MW + 1], any = 0;                              // the row's marks (block-uniform)
 #pragma unroll
     for (int i = 0; i < MW; ++i) any |= mw[i] = mrow[i];
     mw[MW] = 0;
     if (any == 0) return;
-    const int tid = threadIdx.x, line = tid / T, j = tid % T;
+    const int tid = threadIdx.x;
     for (int i = tid; i < TB.second; i += A::kThreads) tab[i] = tw[NP + i];
-    const int half = N / 2;
     // lanes over r: y[n] = W_N'^(-n b) sum_m x[n + F m] W_C^(-m b) of line r,
     // n = n0 + T k; bin f = n + F m carries image row q = (f + N/2) mod N' when
     // that is below N (f < N/2 or f >= N' - N/2)
-    const int r = tid % RW, n0 = tid / RW;
-    const cpx<R>* src = inter + (size_t(t) * inter_blocks(N) * nbr + rt) * 256 + h * RW;      // block-uniform
-    auto at = [&](int q) { return src[uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r)]; };
-    cpx<R> y[16];
+    const int N_ = N, nbr_ = nbr, tid_ = tid;
+    for (int t = first; t < end; ++t) {
+        // the addresses and conditions are formed again for each layer: kept across the
+        // layers they spill
+        int N = N_, nbr = nbr_, tid = tid_;
+        if constexpr (A::kDegridLoop) asm volatile("" : "+s"(N), "+s"(nbr), "+v"(tid));
+        const int half = N / 2, r = tid % RW, n0 = tid / RW, line = tid / T, j = tid % T;
+        const cpx<R>* src = inter + (size_t(t) * inter_blocks(N) * nbr + rt) * 256 + h * RW;      // block-uniform
+        auto at = [&](int q) { return src[uint32_t(q >> 4) * uint32_t(nbr * 256) + uint32_t((q & 15) * 16 + r)]; };
+        cpx<R> y[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) y[k] = cpx<R>{R(0), R(0)};
+        for (int k = 0; k < 16; ++k) y[k] = cpx<R>{R(0), R(0)};
 #pragma unroll
-    for (int m = 0; m < C; ++m) {
-        if (F * m >= half && F * (m + 1) <= NP - half) continue;       // padding bins only
-        cpx<R> x[16];
+        for (int m = 0; m < C; ++m) {
+            if (F * m >= half && F * (m + 1) <= NP - half) continue;       // padding bins only
+            cpx<R> x[16];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int f0 = T * k + F * m;              // the T bins from f0 (block-uniform cases)
-            x[k] = cpx<R>{R(0), R(0)};
-            if (f0 + T <= half) {
-                x[k] = at(n0 + f0 + half);
-            } else if (f0 >= NP - half) {
-                x[k] = at(n0 + f0 + half - NP);
-            } else if (f0 < half || f0 + T > NP - half) {
-                const int q = shift_half<NP>(n0 + f0, half);
-                if (q < N) x[k] = at(q);
+            for (int k = 0; k < 16; ++k) {
+                const int f0 = T * k + F * m;              // the T bins from f0 (block-uniform cases)
+                x[k] = cpx<R>{R(0), R(0)};
+                if (f0 + T <= half) {
+                    x[k] = at(n0 + f0 + half);
+                } else if (f0 >= NP - half) {
+                    x[k] = at(n0 + f0 + half - NP);
+                } else if (f0 < half || f0 + T > NP - half) {
+                    const int q = shift_half<NP>(n0 + f0, half);
+                    if (q < N) x[k] = at(q);
+                }
             }
+            const cpx<R> wm = tw[(m * b % C) * F];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                y[k].x += x[k].x * wm.x + x[k].y * wm.y;
+                y[k].y += x[k].y * wm.x - x[k].x * wm.y;
+            }
+            __builtin_amdgcn_sched_barrier(0);     // 16 loads in flight per thread are enough, more spill
         }
-        const cpx<R> wm = tw[(m * b % C) * F];
+        cpx<R>* lbuf = buf + line * LP;
+        const int pj = lpad(j), pn = lpad(n0);
+        if (t > first) __syncthreads();      // the lines of the layer before are read
+        const cpx<R>* turn_b = tw + NP + TB.entries + b * F;               // W_N'^(n b)
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            y[k].x += x[k].x * wm.x + x[k].y * wm.y;
-            y[k].y += x[k].y * wm.x - x[k].x * wm.y;
+            if (b > 0) {
+                const cpx<R> w = turn_b[n0 + T * k];
+                y[k] = cmul(y[k], cpx<R>{w.x, -w.y});
+            }
+            buf[r * LP + lpad_at<T>(n0, pn, k)] = y[k];
         }
-        __builtin_amdgcn_sched_barrier(0);     // 16 loads in flight per thread are enough, more spill
-    }
-    cpx<R>* lbuf = buf + line * LP;
-    const int pj = lpad(j), pn = lpad(n0);
-    const cpx<R>* turn_b = tw + NP + TB.entries + b * F;               // W_N'^(n b)
+        __syncthreads();
+        cpx<R> v[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        if (b > 0) {
-            const cpx<R> w = turn_b[n0 + T * k];
-            y[k] = cmul(y[k], cpx<R>{w.x, -w.y});
-        }
-        buf[r * LP + lpad_at<T>(n0, pn, k)] = y[k];
-    }
-    __syncthreads();
-    cpx<R> v[16];
+        for (int k = 0; k < 16; ++k) v[k] = lbuf[lpad_at<T>(j, pj, k)];
+        fft_wave<R, F, -1>(v, lbuf, tab, tw + NP + TB.second, j);
+        cpx<R>* dst = stack + (size_t(t) * nbr + rt) * (size_t(NB) * TE);
+        if constexpr (NP % 256 == 0) {
+            // the values k of a thread are NP / 256 tiles apart, at one place within their tiles
+            constexpr int STEP = NP / 256;
+            const int s0 = C * j + b, tile0 = s0 / kTileS;
+            const uint32_t cell = uint32_t(tile0 * TE + degrid_cell<C>(s0, h * RW + line));
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = lbuf[lpad_at<T>(j, pj, k)];
-    fft_wave<R, F, -1>(v, lbuf, tab, tw + NP + TB.second, j);
-    cpx<R>* dst = stack + (size_t(t) * nbr + rt) * (size_t(NB) * TE);
-    if constexpr (NP % 256 == 0) {
-        // the values k of a thread are NP / 256 tiles apart, at one place within their tiles
-        constexpr int STEP = NP / 256;
-        const int s0 = C * j + b, tile0 = s0 / kTileS;
-        const uint32_t cell = uint32_t(tile0 * TE + degrid_cell<C>(s0, h * RW + line));
+            for (int k = 0; k < 16; ++k) {
+                const uint32_t marks = uint32_t(((uint64_t(mw[STEP * k / 32 + 1]) << 32) | mw[STEP * k / 32]) >> (STEP * k % 32));
+                if ((marks >> tile0) & 1u) dst[cell + uint32_t(STEP * k * TE)] = v[k];
+            }
+        } else {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const uint32_t marks = uint32_t(((uint64_t(mw[STEP * k / 32 + 1]) << 32) | mw[STEP * k / 32]) >> (STEP * k % 32));
-            if ((marks >> tile0) & 1u) dst[cell + uint32_t(STEP * k * TE)] = v[k];
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int s = C * (j + T * k) + b, tile = s / kTileS;
-            if ((mw[0] >> tile) & 1u) dst[tile * TE + degrid_cell<C>(s, h * RW + line)] = v[k];
+            for (int k = 0; k < 16; ++k) {
+                const int s = C * (j + T * k) + b, tile = s / kTileS;
+                if ((mw[0] >> tile) & 1u) dst[tile * TE + degrid_cell<C>(s, h * RW + line)] = v[k];
+            }
         }
     }
 }

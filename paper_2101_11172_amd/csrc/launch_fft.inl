@@ -19,6 +19,12 @@ void launch_fft_n(bool grid, const DevParams& P, const uint32_t* mask, const uin
     using C = FftCfg<R, NP>;
     using A = PassACfg<R, NP>;
     const unsigned grid_a = unsigned(P.pln) * unsigned(P.nbr * A::kHalves * A::kClasses);     // a class of kRows lines each
+    // layers of a tile layer that a block takes one after the other, as long as eight
+    // rounds of blocks are left
+    int each = kTileT;
+    while (each > 1 && grid_a / unsigned(each) < 4096u) each /= 2;
+    const unsigned blocks_a = grid_a / unsigned(P.pln) * unsigned((P.pln + each - 1) / each);
+    const unsigned degrid_a = A::kDegridLoop ? blocks_a : grid_a;
     const unsigned grid_b = unsigned((P.N + C::kNLr - 1) / C::kNLr);
     const int chl = P.nbt * kTileT;
     const size_t map = size_t(P.N) * size_t(P.N);
@@ -38,12 +44,7 @@ void launch_fft_n(bool grid, const DevParams& P, const uint32_t* mask, const uin
     if (grid) {
         {
             StageMark mark(s, 2);
-            // layers of a tile layer that a block takes one after the other, as long as eight
-            // rounds of blocks are left
-            int each = kTileT;
-            while (each > 1 && grid_a / unsigned(each) < 4096u) each /= 2;
-            hipLaunchKernelGGL((k_grid_fft_a<R, NP>), dim3(grid_a / unsigned(P.pln) * unsigned((P.pln + each - 1) / each)),
-                               dim3(A::kThreads), 0, s, (const cpx<R>*)stack, mask, inter, tw, P.N, P.n_layers,
+            hipLaunchKernelGGL((k_grid_fft_a<R, NP>), dim3(blocks_a), dim3(A::kThreads), 0, s, (const cpx<R>*)stack, mask, inter, tw, P.N, P.n_layers,
                                P.nch > 1 ? chl : 0, P.nbr, P.pl0, P.pln, each);
         }
         StageMark mark(s, 3);
@@ -70,8 +71,8 @@ void launch_fft_n(bool grid, const DevParams& P, const uint32_t* mask, const uin
             });
         }
         StageMark mark(s, 6);
-        hipLaunchKernelGGL((k_degrid_fft_a<R, NP>), dim3(grid_a), dim3(A::kThreads), 0, s, (const cpx<R>*)inter,
-                           mask, tw, stack, P.N, P.n_layers, P.nch > 1 ? chl : 0, P.nbr, P.pl0);
+        hipLaunchKernelGGL((k_degrid_fft_a<R, NP>), dim3(degrid_a), dim3(A::kThreads), 0, s, (const cpx<R>*)inter,
+                           mask, tw, stack, P.N, P.n_layers, P.nch > 1 ? chl : 0, P.nbr, P.pl0, P.pln, each);
     }
 }
 
