@@ -1709,8 +1709,8 @@ __device__ __forceinline__ int shift_half(int f, int half) {
 // Bound by latency and VALU issue (about half of the issue slots are used, two
 // blocks of 8 waves per CU).  Wide field (N' = 4096, 49 layers, one pass), with
 // the transpose of the intermediate that a whole-line pass needs: FP32 grid
-// 2.13 -> 1.56 ms, degrid 2.06 -> 2.00; FP64 4.55 -> 2.96 and 4.58 -> 3.71;
-// N' = 3072 FP32 degrid 1.63 -> 0.97.  Rows are dealt to the XCDs in turn: the
+// 2.13 -> 1.56 ms, degrid 2.06 -> 1.83; FP64 4.55 -> 2.96 and 4.58 -> 3.43;
+// N' = 3072 FP32 degrid 1.63 -> 0.94.  Rows are dealt to the XCDs in turn: the
 // marked rows thin out towards the upper layers, and with a contiguous range of
 // rows per XCD the grid direction took 2.90 ms.  At kRows = 16 (one block of
 // 1024 threads per CU) FP32 took 2.99 ms.  Twiddles gathered from the table of
