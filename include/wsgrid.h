@@ -152,7 +152,8 @@ int grid_plan_info(const wsg_plan* plan, int* Nprime, int* n_layers, int* t_lo,
  * once: the w-layer stack (n_layers N'^2 complex; only tiles some visibility
  * reaches are touched), the FFT intermediate (n_layers N N' complex, N
  * rounded up to a multiple of 16), the binned visibility records (2 M records), the
- * degrid per-tile parts (8 M complex) and the bin tables.  0 on a bad argument.
+ * degrid per-tile parts (8 M complex), the bin tables and the list of marked
+ * tiles.  0 on a bad argument.
  */
 size_t grid_workspace_bytes(const wsg_plan* plan, wsg_prec prec, int64_t M);
 

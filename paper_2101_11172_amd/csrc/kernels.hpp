@@ -546,17 +546,17 @@ static __global__ void k_tile_occupancy(const uint32_t* __restrict__ start, cons
     }
 }
 
-// The marked tiles in tile order: list[pos[t]] for every marked tile t, pos the
-// exclusive scan of the flags (pos[n] = number of marked tiles).  A tile's ranges
-// are gathered here, once for both directions, so that a tile block needs one
-// load before its records.
+// The marked tiles among [first, first + n) in tile order: list[pos[t] -
+// pos[first]] for every marked tile t, pos the exclusive scan of the flags.  A
+// tile's ranges are gathered here, so that a tile block needs one load before its
+// records.
 static __global__ void k_tile_list(const uint8_t* __restrict__ occ, const uint32_t* __restrict__ pos,
                             const uint32_t* __restrict__ start, const uint32_t* __restrict__ cls, DevParams P,
-                            TileRec* __restrict__ list) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= P.nch * P.nbt * P.nbs * P.nbr || !occ[t]) return;
+                            int first, int n_tiles, TileRec* __restrict__ list) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, t = first + i;
+    if (i >= n_tiles || !occ[t]) return;
     const int br = t % P.nbr, bs = (t / P.nbr) % P.nbs, bt = t / (P.nbr * P.nbs);
-    TileRec& T = list[pos[t]];
+    TileRec& T = list[pos[t] - pos[first]];
     uint32_t total = 0, nbrs = 0;
     int n = 0;
     for (int nb = 0; nb < 8; ++nb) {
@@ -649,7 +649,7 @@ __device__ __forceinline__ int tile_of_block(const DevParams& P, const uint32_t*
     const int per_layer = P.nbs * P.nbr;
     const int nbt_pass = (P.pln + kTileT - 1) / kTileT;
     const int a = (P.pl0 / kTileT) * per_layer, e = a + nbt_pass * per_layer;
-    const int first = int(tpos[a]), cnt = int(tpos[e]) - first;
+    const int cnt = int(tpos[e] - tpos[a]), first = int(tpos[a] - tpos[P.list_from]);
     if (int(blockIdx.x) >= cnt) return -1;
     return first + xcd_interleave<4>(blockIdx.x, cnt);
 }
@@ -1061,7 +1061,8 @@ struct TileRun {
 __device__ __forceinline__ bool tiles_of_block(const DevParams& P, const uint32_t* __restrict__ tpos, int resident,
                                                TileRun& run) {
     const int per_layer = P.nbs * P.nbr, a = (P.pl0 / kTileT) * per_layer;
-    const int first = int(tpos[a]), cnt = int(tpos[a + (P.pln + kTileT - 1) / kTileT * per_layer]) - first;
+    const int cnt = int(tpos[a + (P.pln + kTileT - 1) / kTileT * per_layer] - tpos[a]);
+    const int first = int(tpos[a] - tpos[P.list_from]);
     const int each = min(kMostTiles, max(1, cnt / (2 * resident)));
     run.step = (cnt + each - 1) / each;
     run.place = first + xcd_interleave<4>(blockIdx.x, run.step);

@@ -49,7 +49,7 @@ int fail(int code, const std::string& msg) {
         if (e_ != hipSuccess) return fail(WSG_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-constexpr int kMaxBins = 1 << 25;   // bins over all channels (the bin tables take ~50 bytes per bin)
+constexpr int kMaxBins = 1 << 25;   // bins over all channels (the bin tables take ~46 bytes per bin, beside the lists of marked tiles)
 
 // Workspace of grid_visibilities_noalloc: one file-scope device array, which
 // each device that loads the library holds (its own copy) until the process
@@ -141,9 +141,11 @@ namespace {
 struct Layout {
     size_t stack, inter, rec, rec2, part, count, start, bsums, cls, occ, rows, mask, cleared, chan, tpos, tlist, skipped,
         total;
-    int nch, nbins, nscan;
+    int nch, nbins, nbt, nscan;
     int last_layer;    // end of the last channel's layers on the virtual layer axis
     int pass_layers;   // virtual layers held in the stack and FFT buffers at a time (a multiple of kTileT, or all)
+    bool whole_list;   // one list of marked tiles for all layers, made with the binning; else one per pass
+    int pass_tiles(int layers) const { return (layers + kTileT - 1) / kTileT * (nbins / (nch * nbt)); }
 };
 
 constexpr int kMaxChannels = 64;
@@ -158,8 +160,11 @@ size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 size_t al2m(size_t x) { return (x + (size_t(2) << 20) - 1) & ~((size_t(2) << 20) - 1); }
 
 // Workspace for nch channels (M visibilities in all) taken in passes of
-// `tiles_per_pass` tile layers (kTileT virtual layers each).
-Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass, int nch = 1) {
+// `tiles_per_pass` tile layers (kTileT virtual layers each).  The list of marked
+// tiles takes 128 bytes per tile: it covers a pass's tiles, or all of them with
+// whole_list (taken where the workspace has room, which saves a launch per pass).
+Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass, int nch = 1,
+                 bool whole_list = false) {
     Layout L{};
     const size_t cs = prec == WSG_F32 ? sizeof(cpx<float>) : sizeof(cpx<double>);
     const size_t rs = prec == WSG_F32 ? sizeof(Rec<float>) : sizeof(Rec<double>);
@@ -169,6 +174,9 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     const size_t Np = size_t(p->pp.Nprime), nl = size_t(L.pass_layers);
     L.nbins = nch * p->nbins();
     L.nscan = (L.nbins + 1023) / 1024;
+    L.nbt = p->nbt;
+    L.whole_list = whole_list || L.pass_tiles(L.pass_layers) == L.nbins;
+    const size_t listed = size_t(L.whole_list ? L.nbins : L.pass_tiles(L.pass_layers));
     // the skipped counter sits at offset 0 whatever M and the precision (the next
     // word counts the skipped indices behind the records); what a binning clears comes first
     size_t off = 0;
@@ -182,7 +190,7 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     L.cls = off;     off += al256(size_t(L.nbins) * 8 * 4);
     L.occ = off;     off += al256(size_t(L.nbins));
     L.tpos = off;    off += al256(size_t(L.nbins + 1) * 4);
-    L.tlist = off;   off += al256(std::min(size_t(L.nbins), 8 * size_t(M)) * sizeof(TileRec));   // a record reaches 8 tiles at most
+    L.tlist = off;   off += al256(std::min(listed, 8 * size_t(M)) * sizeof(TileRec));   // a record reaches 8 tiles at most
     L.chan = off;    off += al256(sizeof(long long) * (kMaxChannels + 1));
     // the large buffers start on 2 MiB boundaries (their power-of-two line
     // strides then meet the memory channels the same way whatever precedes them)
@@ -262,6 +270,7 @@ int check_call(const wsg_plan* plan, wsg_prec prec, int nch, const int64_t* Mc, 
     int tiles = nch * plan->nbt;
     *L = layout_of(plan, prec, tot, tiles, nch);
     while (tiles > 1 && ws_bytes < L->total) *L = layout_of(plan, prec, tot, --tiles, nch);
+    if (const Layout whole = layout_of(plan, prec, tot, tiles, nch, true); whole.total <= ws_bytes) *L = whole;
     if (ws_bytes < L->total)
         return fail(WSG_EWORKSPACE, "workspace too small: need at least " + std::to_string(L->total) + " bytes");
     int dev = -1;
@@ -270,9 +279,18 @@ int check_call(const wsg_plan* plan, wsg_prec prec, int nch, const int64_t* Mc, 
     return WSG_OK;
 }
 
+// The list of the marked tiles among tiles [first, first + n).
+void list_tiles(void* ws, const Layout& L, const DevParams& P, int first, int n, int stage, hipStream_t s) {
+    char* w = static_cast<char*>(ws);
+    StageMark mark(s, stage);
+    hipLaunchKernelGGL(k_tile_list, dim3((n + 255) / 256), dim3(256), 0, s, reinterpret_cast<const uint8_t*>(w + L.occ),
+                       reinterpret_cast<const uint32_t*>(w + L.tpos), reinterpret_cast<const uint32_t*>(w + L.start),
+                       reinterpret_cast<const uint32_t*>(w + L.cls), P, first, n, reinterpret_cast<TileRec*>(w + L.tlist));
+}
+
 // Binning (Alg. 5 step 2, Alg. 6 steps 4-5 preprocessing; Sec. 5.4 fold):
 // records binned by tile and sorted by touch class into `rec`, the class
-// starts, the occupancy marks and the ordered tile list.  Grid records carry the
+// starts, the occupancy marks and (where it covers all layers) the ordered tile list.  Grid records carry the
 // phase-rotated visibility, degrid records the phase and the visibility index.
 template <typename R>
 void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, const double* uvw, const void* in,
@@ -290,7 +308,6 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
     auto* rows = reinterpret_cast<uint8_t*>(w + L.rows);
     auto* mask = reinterpret_cast<uint32_t*>(w + L.mask);
     auto* tpos = reinterpret_cast<uint32_t*>(w + L.tpos);
-    auto* tlist = reinterpret_cast<TileRec*>(w + L.tlist);
     auto* coff = reinterpret_cast<long long*>(w + L.chan);
     auto* skipped = reinterpret_cast<uint32_t*>(w + L.skipped);
 
@@ -334,9 +351,8 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
         hipLaunchKernelGGL(k_tile_occupancy, dim3((L.nbins + 255) / 256), dim3(256), 0, s, (const uint32_t*)start,
                            (const uint32_t*)cls, P, occ, rows, mask, count);
         scan(count, tpos, bsums, L.nbins, s);
-        hipLaunchKernelGGL(k_tile_list, dim3((L.nbins + 255) / 256), dim3(256), 0, s, (const uint8_t*)occ,
-                           (const uint32_t*)tpos, (const uint32_t*)start, (const uint32_t*)cls, P, tlist);
     }
+    if (L.whole_list) list_tiles(ws, L, P, 0, L.nbins, stage, s);
 }
 
 // Layer passes over the binned records `rec` (grid: scatter, transforms,
@@ -367,13 +383,14 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
     // pass transforms its layers and gathers from its tiles; every (visibility,
     // tile) part belongs to exactly one pass, and k_degrid_finish sums them at
     // the end.  Virtual layers past a channel's n_layers are padding, skipped.
-    const int per_layer = P.nbs * P.nbr;
     auto* part = reinterpret_cast<cpx<R>*>(w + L.part);
     for (int pl0 = 0; pl0 < L.last_layer; pl0 += L.pass_layers) {
         DevParams Q = P;
         Q.pl0 = pl0;
         Q.pln = std::min(L.pass_layers, L.last_layer - pl0);
-        const int nblocks = ((Q.pln + kTileT - 1) / kTileT) * per_layer;
+        const int nblocks = L.pass_tiles(Q.pln);
+        Q.list_from = L.whole_list ? 0 : pl0 / kTileT * P.nbs * P.nbr;
+        if (!L.whole_list) list_tiles(ws, L, P, Q.list_from, nblocks, grid ? 0 : 4, s);
         if (grid) {
             {
                 StageMark mark(s, 1);
