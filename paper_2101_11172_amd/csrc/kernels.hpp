@@ -244,16 +244,39 @@ __device__ __forceinline__ uint32_t wave_reserve(uint32_t* counter, bool want) {
 // Counts of few visibilities: a thread each, its place in its bin straight from
 // the bin's counter (5,000 visibilities: 11 -> 4 us, 46,332: 17 -> 8).  With more
 // the atomics on the fullest bins wait for each other (120,011: 34 us, 2M: 224).
+// So they do, 11 ns each, where the visibilities lie in few bins (short baselines,
+// small maps: 65,536 in one bin 720 us), so a wave first joins its lanes of one bin,
+// for eight bins, and goes on where these held enough of its lanes (join_lanes):
+// the rest of a wave takes up to 2 us, as long as 150 updates of one counter, which
+// M visibilities bring when eight bins hold 8 + 64 8 150 / M of its lanes.
 constexpr int kDirectThreads = 256;
 static __global__ void __launch_bounds__(kDirectThreads) k_bin_count_direct(const double* __restrict__ uvw,
                                                            const long long* __restrict__ coff, DevParams P,
                                                            uint32_t* __restrict__ count,
-                                                           uint32_t* __restrict__ skipped, uint32_t* __restrict__ rank) {
+                                                           uint32_t* __restrict__ skipped, uint32_t* __restrict__ rank,
+                                                           int join_lanes) {
     const ChunkRange cr = chunk_of_block<kDirectThreads>(coff, P.nch);
     const long long k = cr.k0 + threadIdx.x;
     VisCoords c;
     const bool in = k < cr.k1, ok = in && vis_coords(uvw, k, cr.ch, P, c);
-    if (ok) rank[k] = atomicAdd(&count[bin_of(c, P)], 1u);
+    const int lane = threadIdx.x & 63, b = ok ? bin_of(c, P) : -1;
+    unsigned long long todo = __ballot(ok), group = 1ull << lane;        // the lanes of this lane's bin
+    const int kept = __popcll(todo);
+    auto join = [&]() {                  // the first such lane's bin (none left: no change)
+        const int key = __builtin_amdgcn_readlane(b, int(__builtin_ctzll(todo | (1ull << 63))));
+        const unsigned long long same = __ballot(b == key);
+        if (b == key) group = same;
+        todo &= ~same;
+    };
+#pragma unroll
+    for (int n = 0; n < 8; ++n) join();
+    if (kept - __popcll(todo) >= join_lanes)
+        while (todo != 0ull) join();
+    const int first = __builtin_ctzll(group);
+    uint32_t place = 0;
+    if (ok && lane == first) place = atomicAdd(&count[b], uint32_t(__popcll(group)));
+    place = __shfl(place, first, 64) + uint32_t(__popcll(group & ((1ull << lane) - 1ull)));
+    if (ok) rank[k] = place;
     wave_reserve(skipped, in && !ok);
 }
 

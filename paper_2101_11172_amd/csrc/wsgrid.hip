@@ -332,7 +332,7 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
                                count, skipped, rank);
         else if (M > 0)
             hipLaunchKernelGGL(k_bin_count_direct, blocks(kDirectThreads), dim3(kDirectThreads), 0, s, uvw,
-                               (const long long*)coff, P, count, skipped, rank);
+                               (const long long*)coff, P, count, skipped, rank, 8 + int(64 * 8 * 150 / M));
         scan(count, start, bsums, L.nbins, s);
         if (M > 0) {
             if (grid)
