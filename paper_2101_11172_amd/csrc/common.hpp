@@ -81,7 +81,6 @@ struct DevParams {
     // layer pass: virtual layers [pl0, pl0 + pln) (pl0 a multiple of kTileT)
     // sit in the stack and FFT buffers, local layer index t - pl0
     int pl0, pln;
-    int list_from;          // first tile that the list of marked tiles covers
     int classes;            // pass_a_classes(Np)
     double umul;            // l_max / x0: u -> u'
     double nscale;          // w -> w'

@@ -572,11 +572,16 @@ static __global__ void k_tile_occupancy(const uint32_t* __restrict__ start, cons
 // The marked tiles among [first, first + n) in tile order: list[pos[t] -
 // pos[first]] for every marked tile t, pos the exclusive scan of the flags.  A
 // tile's ranges are gathered here, so that a tile block needs one load before its
-// records.
+// records.  pass: null, or where the tile kernels find the bounds of a list that
+// starts with tile `first`, as in pos.
 static __global__ void k_tile_list(const uint8_t* __restrict__ occ, const uint32_t* __restrict__ pos,
                             const uint32_t* __restrict__ start, const uint32_t* __restrict__ cls, DevParams P,
-                            int first, int n_tiles, TileRec* __restrict__ list) {
+                            int first, int n_tiles, uint32_t* __restrict__ pass, TileRec* __restrict__ list) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, t = first + i;
+    if (i == 0 && pass) {
+        pass[first] = 0u;
+        pass[first + n_tiles] = pos[first + n_tiles] - pos[first];
+    }
     if (i >= n_tiles || !occ[t]) return;
     const int br = t % P.nbr, bs = (t / P.nbr) % P.nbs, bt = t / (P.nbr * P.nbs);
     TileRec& T = list[pos[t] - pos[first]];
@@ -672,7 +677,7 @@ __device__ __forceinline__ int tile_of_block(const DevParams& P, const uint32_t*
     const int per_layer = P.nbs * P.nbr;
     const int nbt_pass = (P.pln + kTileT - 1) / kTileT;
     const int a = (P.pl0 / kTileT) * per_layer, e = a + nbt_pass * per_layer;
-    const int cnt = int(tpos[e] - tpos[a]), first = int(tpos[a] - tpos[P.list_from]);
+    const int first = int(tpos[a]), cnt = int(tpos[e]) - first;
     if (int(blockIdx.x) >= cnt) return -1;
     return first + xcd_interleave<4>(blockIdx.x, cnt);
 }
@@ -1084,8 +1089,7 @@ struct TileRun {
 __device__ __forceinline__ bool tiles_of_block(const DevParams& P, const uint32_t* __restrict__ tpos, int resident,
                                                TileRun& run) {
     const int per_layer = P.nbs * P.nbr, a = (P.pl0 / kTileT) * per_layer;
-    const int cnt = int(tpos[a + (P.pln + kTileT - 1) / kTileT * per_layer] - tpos[a]);
-    const int first = int(tpos[a] - tpos[P.list_from]);
+    const int first = int(tpos[a]), cnt = int(tpos[a + (P.pln + kTileT - 1) / kTileT * per_layer]) - first;
     const int each = min(kMostTiles, max(1, cnt / (2 * resident)));
     run.step = (cnt + each - 1) / each;
     run.place = first + xcd_interleave<4>(blockIdx.x, run.step);

@@ -181,7 +181,7 @@ Layout layout_of(const wsg_plan* p, wsg_prec prec, int64_t M, int tiles_per_pass
     // word counts the skipped indices behind the records); what a binning clears comes first
     size_t off = 0;
     L.skipped = off; off += 256;
-    L.count = off;   off += al256(size_t(L.nbins) * 4);
+    L.count = off;   off += al256(size_t(L.nbins + 1) * 4);
     L.rows = off;    off += al256(size_t(nch) * p->nbt * p->nbr);
     L.mask = off;    off += al256(size_t(nch) * p->nbt * p->nbr * mask_words(p->nbs) * 4);
     L.cleared = off;
@@ -279,13 +279,16 @@ int check_call(const wsg_plan* plan, wsg_prec prec, int nch, const int64_t* Mc, 
     return WSG_OK;
 }
 
-// The list of the marked tiles among tiles [first, first + n).
+// The list of the marked tiles among tiles [first, first + n), its bounds for a pass
+// left in the bin counts (free by then).
 void list_tiles(void* ws, const Layout& L, const DevParams& P, int first, int n, int stage, hipStream_t s) {
     char* w = static_cast<char*>(ws);
     StageMark mark(s, stage);
     hipLaunchKernelGGL(k_tile_list, dim3((n + 255) / 256), dim3(256), 0, s, reinterpret_cast<const uint8_t*>(w + L.occ),
                        reinterpret_cast<const uint32_t*>(w + L.tpos), reinterpret_cast<const uint32_t*>(w + L.start),
-                       reinterpret_cast<const uint32_t*>(w + L.cls), P, first, n, reinterpret_cast<TileRec*>(w + L.tlist));
+                       reinterpret_cast<const uint32_t*>(w + L.cls), P, first, n,
+                       L.whole_list ? nullptr : reinterpret_cast<uint32_t*>(w + L.count),
+                       reinterpret_cast<TileRec*>(w + L.tlist));
 }
 
 // Binning (Alg. 5 step 2, Alg. 6 steps 4-5 preprocessing; Sec. 5.4 fold):
@@ -369,7 +372,7 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
     auto* start = reinterpret_cast<uint32_t*>(w + L.start);
     auto* rows = reinterpret_cast<uint8_t*>(w + L.rows);
     auto* mask = reinterpret_cast<uint32_t*>(w + L.mask);
-    auto* tpos = reinterpret_cast<uint32_t*>(w + L.tpos);
+    auto* tpos = reinterpret_cast<uint32_t*>(w + (L.whole_list ? L.tpos : L.count));
     auto* tlist = reinterpret_cast<TileRec*>(w + L.tlist);
     const bool f64 = sizeof(R) == 8;
     const R* coef = f64 ? reinterpret_cast<const R*>(plan->poly64) : reinterpret_cast<const R*>(plan->poly32);
@@ -389,8 +392,7 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
         Q.pl0 = pl0;
         Q.pln = std::min(L.pass_layers, L.last_layer - pl0);
         const int nblocks = L.pass_tiles(Q.pln);
-        Q.list_from = L.whole_list ? 0 : pl0 / kTileT * P.nbs * P.nbr;
-        if (!L.whole_list) list_tiles(ws, L, P, Q.list_from, nblocks, grid ? 0 : 4, s);
+        if (!L.whole_list) list_tiles(ws, L, P, pl0 / kTileT * P.nbs * P.nbr, nblocks, grid ? 0 : 4, s);
         if (grid) {
             {
                 StageMark mark(s, 1);
