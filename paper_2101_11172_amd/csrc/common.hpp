@@ -82,6 +82,7 @@ struct DevParams {
     // sit in the stack and FFT buffers, local layer index t - pl0
     int pl0, pln;
     int classes;            // pass_a_classes(Np)
+    int euv, et;            // window blocks' starts along u, v and along w by which records are ordered (1: by start)
     double umul;            // l_max / x0: u -> u'
     double nscale;          // w -> w'
     double zshift;          // (1 - n0) / n_scale: z = (n - 1) / n_scale + zshift
@@ -90,6 +91,18 @@ struct DevParams {
 };
 
 constexpr int kTileR = 16, kTileS = 16, kTileT = 16;
+
+// Windows.  The matrix kernels of width W <= 8 work on windows of kWin = 8 cells
+// along each axis, which hold the support of every record whose start lies in
+// the window's first 9 - W cells: a class's part of an axis is cut into blocks
+// of window_edge starts, and a class's records are ordered by block (layer, u,
+// v), then by start, where a kernel on windows reads them, else by start alone.
+constexpr int kWin = 8;
+__host__ __device__ constexpr int window_edge(int W) { return W <= kWin ? kWin + 1 - W : 1; }
+
+// Whether the scatter, and the gather, of these widths is the matrix kernel.
+__host__ __device__ constexpr bool mat_scatter(bool f64, int W, int Wz) { return W <= kWin; }
+__host__ __device__ constexpr bool mat_gather(bool f64, int W, int Wz) { return f64 && W <= kWin; }
 
 // Words of the marks of one row of nbs tiles.
 __host__ __device__ constexpr int mask_words(int nbs) { return (nbs + 31) / 32; }

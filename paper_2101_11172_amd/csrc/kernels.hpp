@@ -454,13 +454,6 @@ __device__ __forceinline__ int class_base(int q, int Bt, int Buv) {
     return b;
 }
 
-// Windows.  The tile kernels of width W <= 8 work on windows of kWin = 8 cells
-// along each axis, which hold the support of every record whose start lies in
-// the window's first 9 - W cells: a class's part of an axis is cut into blocks
-// of window_edge starts, and a class's records are ordered by block (layer, u,
-// v), then by start.  W > 8: blocks of one start.
-constexpr int kWin = 8;
-__host__ __device__ constexpr int window_edge(int W) { return W <= kWin ? kWin + 1 - W : 1; }
 // first start of the block of start i (of its class's part), and its size
 __device__ __forceinline__ int block_start(int i, int edge) { return i / edge * edge; }
 
@@ -486,7 +479,7 @@ __global__ void __launch_bounds__(256) k_bin_local_sort(const Rec<R>* __restrict
     if (tid < 9) cbase[tid] = class_base(tid, Bt, Buv);
     if (tid >= 32 && tid < 64) {
         const int ax = (tid >> 4) & 1, l = tid & 15, B = ax ? Buv : Bt;
-        const int edge = P.W <= kWin ? window_edge(ax ? P.W : P.Wz) : 1;
+        const int edge = ax ? P.euv : P.et;
         const int hi = l >= B, i = hi ? l - B : l, b = block_start(i, edge);
         blk[ax][l] = b | min(edge, class_part(hi, B) - b) << 8 | (i - b) << 16;
     }
@@ -1328,11 +1321,6 @@ struct MatGatherCfg {
     static constexpr int kLT = kTileR * kTileS + 2;              // cells between layers: a window's layers meet
                                                                  // distinct banks
 };
-template <typename R, int W>
-constexpr bool mat_gather() {
-    return sizeof(R) == 8 && W <= kWin;
-}
-
 // x of the lane n places back in its row of 16 (rotating)
 template <int N>
 __device__ __forceinline__ double row_ror(double x) {

@@ -19,9 +19,9 @@ namespace wsg {
 template <typename R, int W, int WZ, bool SAME>
 void launch_tiles_w(bool grid, int nblocks, const Rec<R>* rec, const TileRec* tlist, const uint32_t* tpos, const DevParams& P, const R* coef, const R* coefz,
                     const cpx<R>* vis, cpx<R>* stack, cpx<R>* part, size_t part_stride, hipStream_t s) {
-    if (grid && W <= kWin) {
-        // the matrix kernel, wherever the window of 8 cells holds the support
-        if constexpr (W <= kWin) {
+    constexpr bool f64 = sizeof(R) == 8;
+    if (grid) {
+        if constexpr (mat_scatter(f64, W, WZ)) {
             constexpr int TH = MatScatterCfg<R, W, WZ>::kThreads;
             if (vis)
                 hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec,
@@ -29,9 +29,7 @@ void launch_tiles_w(bool grid, int nblocks, const Rec<R>* rec, const TileRec* tl
             else
                 hipLaunchKernelGGL((k_grid_tiles_mat<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec,
                                    tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
-        }
-    } else if (grid) {
-        if constexpr (W > kWin) {
+        } else {
             constexpr int TH = ScatterCfg<R, W, WZ>::kThreads;
             if (vis)
                 hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, true>), dim3(nblocks), dim3(TH), 0, s, rec,
@@ -40,7 +38,7 @@ void launch_tiles_w(bool grid, int nblocks, const Rec<R>* rec, const TileRec* tl
                 hipLaunchKernelGGL((k_grid_tiles<R, W, WZ, SAME, false>), dim3(nblocks), dim3(TH), 0, s, rec,
                                    tlist, tpos, P, coef, coefz, (const cpx<R>*)nullptr, stack);
         }
-    } else if constexpr (mat_gather<R, W>()) {
+    } else if constexpr (mat_gather(f64, W, WZ)) {
         hipLaunchKernelGGL((k_degrid_tiles_mat<R, W, WZ, SAME>), dim3(nblocks), dim3(MatGatherCfg<R>::kThreads), 0, s,
                            rec, tlist, tpos, P, coef, coefz, (const cpx<R>*)stack, part, part_stride);
     } else {

@@ -222,6 +222,7 @@ DevParams dev_params(const wsg_plan* p) {
     P.pl0 = 0;
     P.pln = p->pp.n_layers();
     P.classes = pass_a_classes(p->pp.Nprime);
+    P.euv = P.et = 1;
     P.umul = p->pp.l_max / p->pp.x0;
     P.nscale = p->pp.n_scale;
     P.zshift = p->pp.z_shift;
@@ -297,9 +298,14 @@ void list_tiles(void* ws, const Layout& L, const DevParams& P, int first, int n,
 // phase-rotated visibility, degrid records the phase and the visibility index.
 template <typename R>
 void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, const double* uvw, const void* in,
-               void* ws, const Layout& L, hipStream_t s) {
+               void* ws, const Layout& L, hipStream_t s, bool shared = false) {
     DevParams P = dev_params(plan);
     P.nch = L.nch;
+    const bool f64 = sizeof(R) == 8;
+    if ((!grid && mat_gather(f64, P.W, P.Wz)) || ((grid || shared) && mat_scatter(f64, P.W, P.Wz))) {
+        P.euv = window_edge(P.W);
+        P.et = window_edge(P.Wz);
+    }
     char* w = static_cast<char*>(ws);
     auto* rec_bin = reinterpret_cast<Rec<R>*>(w + L.rec2);   // binned, unordered within a bin
     auto* rec = reinterpret_cast<Rec<R>*>(w + L.rec);        // binned and sorted within each bin
@@ -783,9 +789,9 @@ int grid_prepare(const wsg_plan* plan, wsg_prec prec, int nch, const int64_t* M,
     hipStream_t s = static_cast<hipStream_t>(stream);
     remember_call(plan, ws, stream);
     if (prec == WSG_F32)
-        bin_stage<float>(plan, false, 4, M, uvw, nullptr, ws, L, s);
+        bin_stage<float>(plan, false, 4, M, uvw, nullptr, ws, L, s, true);
     else
-        bin_stage<double>(plan, false, 4, M, uvw, nullptr, ws, L, s);
+        bin_stage<double>(plan, false, 4, M, uvw, nullptr, ws, L, s, true);
     WSG_HIP(hipGetLastError());
     std::lock_guard<std::mutex> g(plan->last_mu);
     plan->prep_ws = ws;
