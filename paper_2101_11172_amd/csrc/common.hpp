@@ -100,9 +100,30 @@ constexpr int kTileR = 16, kTileS = 16, kTileT = 16;
 constexpr int kWin = 8;
 __host__ __device__ constexpr int window_edge(int W) { return W <= kWin ? kWin + 1 - W : 1; }
 
-// Whether the scatter, and the gather, of these widths is the matrix kernel.
-__host__ __device__ constexpr bool mat_scatter(bool f64, int W, int Wz) { return W <= kWin; }
-__host__ __device__ constexpr bool mat_gather(bool f64, int W, int Wz) { return f64 && W <= kWin; }
+// Whether the scatter, and the gather, of these widths is the matrix kernel, else
+// the kernel whose lanes own residues (scatter) or records (gather).  The matrix
+// kernels' work hardly falls with the widths: they take windows of 8 cells per axis
+// whatever the support.  Stage times in us, matrix against lanes, on Earth-rotation
+// tracks (3.3M at 2048^2 and 1M at 1024^2) and 20,000 scattered visibilities:
+//   scatter FP32  (W, W_z) = (2, 2): 561/419, 158/127, 23/19; (3, 3): 603/488, 160/157,
+//                 23/23, 65,536 scattered 29/39; (4, 4): 639/571, 168/207, 23/35; (7, 1):
+//                 742/565, 250/192, 31/28; (8, 1): 916/692, 349/232, 34/38; (7, 2):
+//                 760/659, 248/244, 29/39; (7, 7): 930/1371, 268/546, 31/89
+//   scatter FP64  (2, 2): 777/867, 267/253, 26/21; (7, 1): 1128/1224, 428/351, 37/24, and
+//                 70/50 on 46,332 visibilities of snapshots (original W-stacking); (8, 1):
+//                 1426/1914, 576/562, 40/37; (7, 2): 1164/1355, 432/391, 38/28; (7, 7):
+//                 1360/1864, 452/513, 38/39
+//   gather FP64   (4, 4): 1092/859, 364/234, 40/25; (5, 5): 1210/1029, 395/272, 47/30;
+//                 (6, 6): 1394/1719, 482/452, 53/48; (7, 7): 1696/2912, 606/750, 58/71;
+//                 (5, 1): 1491/839, 502/242, 48/26; (6, 1): 1634/3100, 597/899, 54/82; (8, 1):
+//                 2325/2571, 959/743, 62/60
+// Many visibilities in few bins favour the matrix scatter at every width (65,536 in
+// one bin, W = 2 225/537, W = 7 450/1529) and the lanes' gather up to W = 5 (834/390).
+// In FP32 the gather is better off with lanes at every width (see k_degrid_tiles_mat).
+__host__ __device__ constexpr bool mat_scatter(bool f64, int W, int Wz) {
+    return W <= kWin && (f64 ? W != 7 || Wz > 1 : W > 2 && Wz > 1);
+}
+__host__ __device__ constexpr bool mat_gather(bool f64, int W, int Wz) { return f64 && W >= 6 && W <= kWin; }
 
 // Words of the marks of one row of nbs tiles.
 __host__ __device__ constexpr int mask_words(int nbs) { return (nbs + 31) / 32; }

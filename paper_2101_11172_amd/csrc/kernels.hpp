@@ -745,8 +745,9 @@ __device__ __forceinline__ double bits_to_word(int v, double) { return __hiloint
 __device__ __forceinline__ int word_bits(float v) { return __float_as_int(v); }
 __device__ __forceinline__ int word_bits(double v) { return __double2loint(v); }
 
-// Scatter for W > 8, where a window of 8 cells does not hold the support:
-// residue classes (Romein 2012, extended to three axes).  Lane (x, y)
+// Scatter where the matrix kernel is not the better one (mat_scatter), or a window
+// of 8 cells does not hold the support (W > 8): residue classes (Romein 2012,
+// extended to three axes).  Lane (x, y)
 // owns, among the W x W x WZ support cells of a record, the WZ cells whose u
 // and v indices are congruent to x and y modulo W, one per layer residue a: for
 // support start (dr, ds, dt) the u-cell dr + ((x - dr) mod W), the v-cell
@@ -1069,7 +1070,7 @@ struct Mfma<double> {
     }
 };
 
-// Scatter for W <= 8: over the records of one window the sums
+// Scatter for W <= 8 (mat_scatter): over the records of one window the sums
 //     cell (x, y, a) += sum_k [wu_k(x) wv_k(y)] [wt_k(a) V_k]
 // are a product of a 64 x K matrix (rows the window's 8 x 8 pairs (x, y)) with a
 // K x 16 one (columns the 8 layers a times real and imaginary), four 16 x 16 x 4
@@ -1336,7 +1337,7 @@ __global__ void __launch_bounds__((MatScatterCfg<R, W, WZ>::kThreads)) k_grid_ti
     }
 }
 
-// FP64 gather for W <= 8: for the records k of one window
+// FP64 gather for W = 6 to 8 (mat_gather): for the records k of one window
 //     out_k = sum_a wt_k(a) sum_(x, y) [wu_k(x) wv_k(y)] cell(x, y, a)
 // the inner sums are a product of a K x 64 matrix (rows 16 records, columns the
 // window's pairs (x, y)) with a 64 x 16 one (columns the 8 layers times real and
@@ -1562,13 +1563,13 @@ __global__ void __launch_bounds__((MatGatherCfg<R>::kThreads)) __attribute__((am
     }
 }
 
-// Gather in FP32, and in FP64 for W > 8: lanes over records.  The tile sits in LDS as complex cells, rows
-// kLR = 17 cells and layers kLT = 16 kLR + 1 cells apart (the padding cells are
-// zero), with a zero guard of (kLR + 1)(W - 1) cells before and after, so that
-// for any support start (dr, ds) in [-(W-1), 15] the cell address
-// base + kLR x + y of every support offset is inside the array.  Each lane
-// evaluates its own record's weights, sets those of out-of-tile indices to zero
-// (the cells read there are finite neighbours or zeros), clamps the layer of
+// Gather in FP32, and in FP64 for W < 6 and W > 8: lanes over records.  The tile
+// sits in LDS as complex cells, rows kLR = 17 cells and layers kLT = 16 kLR + 1
+// cells apart (the padding cells are zero), with a zero guard of (kLR + 1)(W - 1)
+// cells before and after, so that for any support start (dr, ds) in [-(W-1), 15]
+// the cell address base + kLR x + y of every support offset is inside the array.
+// Each lane evaluates its own record's weights, sets those of out-of-tile indices
+// to zero (the cells read there are finite neighbours or zeros), clamps the layer of
 // each residue and sums the W^3 products; no cross-lane reduction is needed.
 template <typename R, int W>
 struct GatherCfg {
