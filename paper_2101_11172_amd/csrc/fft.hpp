@@ -147,6 +147,13 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
     constexpr int REM = LOG2 % 4;
     const int pj = lpad(j);
     int Ns = 1;
+    // FP64, 2^a points from 512: a pass's twiddles are asked for while its inputs are
+    // exchanged, when the inputs' registers are free; read as they are used, with few
+    // registers left, each is waited for (grid pass B at N' = 4096, 39 layers 1587 ->
+    // 1279 us, 16 layers at a time 2583 -> 1834).  Shorter lines, and with the radix-3
+    // pass, the spills weigh more (N' = 3072 degrid 1226 -> 1472).
+    constexpr bool AHEAD = sizeof(R) == 8 && !R3 && N >= 512;
+    cpx<R> w[AHEAD ? 16 : 1];
 #pragma unroll
     for (int p = 0; p < P16; ++p) {
         if (p > 0) {
@@ -154,7 +161,7 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
             for (int m = 0; m < 16; ++m) v[m] = buf[lpad_at<T>(j, pj, m)];
             const int k = j & (Ns - 1);
 #pragma unroll
-            for (int m = 1; m < 16; ++m) v[m] = cmul(v[m], twiddle<R, DIR>(tab, m * Ns + k));
+            for (int m = 1; m < 16; ++m) v[m] = cmul(v[m], AHEAD ? w[AHEAD ? m : 0] : twiddle<R, DIR>(tab, m * Ns + k));
             tab += 16 * Ns;
         }
         dft16<R, DIR>(v);
@@ -163,8 +170,18 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
         const int base = (j / Ns) * Ns * 16 + (j & (Ns - 1)), pb = lpad(base);
 #pragma unroll
         for (int m = 0; m < 16; ++m) buf[p == 0 ? pb + m : pb + m * (Ns + Ns / 16)] = v[m];     // lpad(base + m Ns)
-        __syncthreads();
         Ns *= 16;
+        if constexpr (AHEAD) {
+            if (p + 1 < P16) {
+#pragma unroll
+                for (int m = 1; m < 16; ++m) w[m] = twiddle<R, DIR>(tab, m * Ns + (j & (Ns - 1)));
+            } else if constexpr (REM > 0) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (i & ((1 << REM) - 1)) w[i] = twiddle<R, DIR>(tab, (i & ((1 << REM) - 1)) * Ns + ((j + (i >> REM) * T) & (Ns - 1)));
+            }
+        }
+        __syncthreads();
     }
     if constexpr (REM > 0) {
         constexpr int RR = 1 << REM;      // radix of this pass
@@ -178,7 +195,8 @@ __device__ __forceinline__ void fft_line(cpx<R> (&v)[16], cpx<R>* buf, const cpx
         for (int b = 0; b < B; ++b) {
             const int k = (j + b * T) & (Ns - 1);
 #pragma unroll
-            for (int m = 1; m < RR; ++m) u[b * RR + m] = cmul(u[b * RR + m], twiddle<R, DIR>(tab, m * Ns + k));
+            for (int m = 1; m < RR; ++m)
+                u[b * RR + m] = cmul(u[b * RR + m], AHEAD ? w[AHEAD ? b * RR + m : 0] : twiddle<R, DIR>(tab, m * Ns + k));
             if constexpr (RR == 2) dft2<R, DIR>(u[b * RR], u[b * RR + 1]);
             if constexpr (RR == 4) dft4<R, DIR>(u[b * RR], u[b * RR + 1], u[b * RR + 2], u[b * RR + 3]);
             if constexpr (RR == 8) dft8<R, DIR>(&u[b * RR]);

@@ -2042,8 +2042,12 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T)) __at
         // FP64 reads the twiddles again for each layer: kept in registers across the layers
         // (30 of them) they left one wave per SIMD (wide field: grid 2.15 -> 1.94 ms, degrid
         // 2.10 -> 1.69).  In FP32 they stay (read again: 0.78 -> 0.86 and 0.71 -> 0.86 ms).
-        const cpx<R>*root = tw, *tab = tw + line_table_at(NP);
-        if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(root), "+s"(tab));
+        // The offset is hidden from the compiler, not the pointers, whose loads would then be
+        // flat ones, which wait for the LDS.  The FP64 kernel holds 256 registers and spills
+        // up to 58 words a thread (N' = 3 2^a; 40 at 4096), most of them z.
+        int again = 0;
+        if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(again));
+        const cpx<R>*root = tw + again, *tab = root + line_table_at(NP);
         fft_line<R, NP, +1>(v, lbuf, root, tab, j);
         const double tl = double(tloc0 + t + P.t_lo) + P.tphase;
 #pragma unroll
@@ -2129,8 +2133,9 @@ __global__ void __launch_bounds__((FftCfg<R, NP>::kNLr * FftCfg<R, NP>::T))
             phase_turns(-tl * z[k], &s, &c);
             v[k] = cpx<R>{g[k] * c, g[k] * s};
         }
-        const cpx<R>*root = tw, *tab = tw + line_table_at(NP);
-        if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(root), "+s"(tab));     // as in k_grid_fft_b
+        int again = 0;
+        if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(again));      // as in k_grid_fft_b
+        const cpx<R>*root = tw + again, *tab = root + line_table_at(NP);
         fft_line<R, NP, -1>(v, lbuf, root, tab, j);
         if (row_ok) {
             // only frequencies r of rows of tiles with an occupied tile are used later
