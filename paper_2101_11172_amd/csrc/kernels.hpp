@@ -1866,7 +1866,7 @@ __global__ void __launch_bounds__((PassACfg<R, NP>::kThreads)) __attribute__((am
                 n += __popcll(all);
             }
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) none |= uint32_t(__shfl_xor(int(none), o, 64));
+            for (int o = (TH < 64 ? TH : 64) / 2; o > 0; o >>= 1) none |= uint32_t(__shfl_xor(int(none), o, 64));
             if (lane == 0) {
                 count[w] = n;
                 empty[w] = none;
