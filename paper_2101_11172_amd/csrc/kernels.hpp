@@ -43,8 +43,9 @@ static __global__ void __launch_bounds__(kProbeThreads) k_copy_probe(const probe
 // v' = (m_max/y0) v, w' = n_scale w (Sec. 5.2), and for each axis the first
 // support index F - W + 1 with F = floor(xi + W/2) and the offset
 // nu = xi + W/2 - F - 1/2 (Sec. 3.3).  Products and sums are rounded one by one
-// (no fused multiply-add) so that the support decision matches a plain
-// evaluation of the same formulas.
+// (contraction off: __dmul_rn and __dadd_rn are plain operators here, which the
+// compiler may fuse) so that the support decision matches a plain evaluation of
+// the same formulas, in every kernel that makes it.
 struct VisCoords {
     int ru, rv, rt;
     double nu_u, nu_v, nu_w;
@@ -53,10 +54,11 @@ struct VisCoords {
 };
 
 __device__ __forceinline__ bool axis_support(double xi, int W, double& nu, long long& first) {
+#pragma clang fp contract(off)
     double hw = 0.5 * W;
-    double t = __dadd_rn(xi, hw);
+    double t = xi + hw;
     double F = floor(t);
-    nu = __dadd_rn(__dadd_rn(t, -F), -0.5);
+    nu = (t - F) - 0.5;
     first = (long long)F - W + 1;
     return true;
 }
@@ -76,6 +78,7 @@ __device__ __forceinline__ int residue(double f, int n) {
 // ch: the visibility's channel (virtual layer offset ch nbt kTileT)
 __device__ __forceinline__ bool vis_coords_of(double u, double v, double w, int ch, const DevParams& P,
                                               VisCoords& c) {
+#pragma clang fp contract(off)
     if (!isfinite(u) || !isfinite(v) || !isfinite(w)) return false;
     c.folded = w < 0.0;
     if (c.folded) {
@@ -84,7 +87,7 @@ __device__ __forceinline__ bool vis_coords_of(double u, double v, double w, int 
         w = -w;
     }
     if (w > P.wmax) return false;
-    double up = __dmul_rn(P.umul, u), vp = __dmul_rn(P.umul, v), wp = __dadd_rn(__dmul_rn(P.nscale, w), P.wshift);
+    const double up = P.umul * u, vp = P.umul * v, wp = P.nscale * w + P.wshift;
     if (fabs(up) > 1e15 || fabs(vp) > 1e15) return false;
     long long fu, fv, ft;
     axis_support(up, P.W, c.nu_u, fu);
