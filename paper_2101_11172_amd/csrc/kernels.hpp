@@ -1792,10 +1792,11 @@ struct PassACfg {
     static constexpr int kThreads = kRows * T;
     static constexpr int kWaves = kThreads < kMost ? 1 : sizeof(R) == 8 ? 2 : 4;     // per SIMD, as two full blocks hold
     static_assert(T <= 64 && 64 % T == 0 && (F & (F - 1)) == 0, "a line's lanes lie in one wave");
-    // degrid blocks that take several layers: at N' = 2048, 3072 and 4096 (one layer each: 2.00 ->
-    // 1.83 ms at wide field, FP64 3.81 -> 3.43); with the loop's registers N' = 8192 (8 classes)
-    // and the shorter transforms took 2-6 % longer
-    static constexpr bool kDegridLoop = F == 1024 && kClasses >= 2 && kClasses <= 4;
+    // degrid blocks that take several layers: from N' = 2048 to 6144 (one layer each: 2.00 ->
+    // 1.83 ms at wide field, FP64 3.81 -> 3.43; N' = 6144 4.23 -> 4.20 and 8.20 -> 7.87); with the
+    // loop's registers N' = 8192 (8 classes) and the shorter transforms took 2-6 % longer, N' = 1024
+    // 3 % (FP32; 2 % less in FP64)
+    static constexpr bool kDegridLoop = F == 1024 && kClasses >= 2 && kClasses <= 6;
     // line stride in LDS: the transposed accesses of kRows lines meet distinct banks
     static constexpr int kBanks = 256 / int(sizeof(cpx<R>));
     static constexpr int LP = (LinePad<F>::size + kBanks - 1) / kBanks * kBanks + (kBanks >= kRows ? kBanks / kRows : 1);
