@@ -89,8 +89,6 @@ def stage_bytes(st: str, M: int, N: int, Np: int, nl: int, f64: bool, ws: dict, 
         # reads the visibility the record names
         "grid_tiles": ws["tile_visits"] * (rec + (b if prepared else 0)) + tiles,
         "grid_fft_v": tiles + inter_rows,               # occupied tiles in, lines of occupied rows out
-        "grid_transpose": inter_rows + inter_rows,      # live lines in and out (the others are zero)
-        "degrid_transpose": inter_rows + inter_rows,    # lines the transform along q needs, in and out
         "grid_fft_u": inter_rows + 2 * N * N * r,       # live intermediate, correction in, map out
         "degrid_bin": M * (2 * 24 + rec) + sort,
         "degrid_fft_p": 2 * N * N * r + inter_rows,     # image, correction in, live intermediate out

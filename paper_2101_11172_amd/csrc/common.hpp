@@ -129,7 +129,16 @@ __host__ __device__ constexpr bool mat_gather(bool f64, int W, int Wz) { return 
 __host__ __device__ constexpr int mask_words(int nbs) { return (nbs + 31) / 32; }
 
 // Classes of outputs that FFT pass A splits a line of N' cells into (the
-// transforms inside a class have at most 1024 points, without a factor 3).
+// transforms inside a class have at most 1024 points, without a factor 3), at
+// every N'.  Against the whole-line pass and the transpose of the intermediate that
+// it needs, 39 layers, grid / degrid in ms: N' = 6144 FP32 5.87 -> 3.17 / 5.72 ->
+// 4.20, FP64 17.3 -> 6.1 / 20.1 -> 7.9; N' = 8192 with N = 4096 8.47 -> 5.69 / 8.86 ->
+// 7.88, FP64 21.4 -> 11.9 / 24.3 -> 16.0, with N = 8192 9.98 -> 7.05 / 10.5 -> 11.7,
+// FP64 29.1 -> 13.8 / 32.6 -> 23.9.  The FP32 degrid direction at N' = 8192 is the
+// one place where it is slower (also three passes of 128-antenna tracks at 4096^2:
+// 20.6 -> 21.8): each of the eight classes reads and multiplies the whole line.  It
+// stays: the calls are not slower, and the whole-line pass wants a second
+// intermediate in the workspace.
 __host__ __device__ constexpr int pass_a_classes(int Np) {
     const int p2 = Np % 3 == 0 ? Np / 3 : Np;
     return (Np % 3 == 0 ? 3 : 1) * (p2 > 1024 ? p2 / 1024 : 1);

@@ -620,14 +620,15 @@ static __global__ void k_tile_list(const uint8_t* __restrict__ occ, const uint32
 
 // ------------------------------------------------ 3-D scatter / gather tiles --
 //
-// One 256-thread block owns one tile of kTileT layers x kTileR u-cells x
-// kTileS v-cells of the stack (layout [t][r][s], s fastest), held in LDS.  The
-// records that reach the tile (from its own bin and the seven bins one tile
-// back, selected by touch class) form a virtual list of at most 64 ranges of
-// the record array.  The list is cut into four contiguous quarters, one per
-// wave; the waves work independently between the tile's set-up and its
-// write-out, and each holds its next records in registers while it works on
-// the current ones.  Each tile is read or written to HBM once.
+// A block holds one tile of kTileT layers x kTileR u-cells x kTileS v-cells of the
+// stack at a time in LDS; the matrix kernels take several tiles one after the
+// other (tiles_of_block).  The records that reach the tile (from its own bin and
+// the seven bins one tile back, selected by touch class) form a virtual list of
+// at most ten ranges of the record array (TileRec).  The list is cut into
+// contiguous parts, one per wave (eight waves in the FP32 matrix scatter, four
+// elsewhere); the waves work independently between the tile's set-up and its
+// write-out, and each holds its next records in registers while it works on the
+// current ones.  Each tile is read or written to HBM once.
 
 // Kernel polynomial degree in nu per precision (the host fits both).
 template <typename R>
@@ -1736,13 +1737,14 @@ __global__ void k_degrid_finish(const Rec<R>* __restrict__ rec, const uint32_t* 
 // --------------------------------------------------------------- FFT passes --
 //
 // The stack is tiled: [t][u tile][v tile][16 x 16 cells], [r][s] within a tile
-// in the grid direction (tile_elems).  Pass A transforms along s and writes
-// (reads, in the degrid direction) the intermediate [t][q][r] in segments of
-// 16 consecutive r, pass B transforms its whole lines along r (q is the image
-// row).  Image rows j <-> q and columns i <-> p.  The FFT output bin
-// f of a line maps to image index (f + N/2) mod N' and is kept when below N
-// (Algorithm 5 step 3c); the degrid input places image index p at bin
-// (p - N/2) mod N' (zero padding, Algorithm 6 step 3b).
+// in the grid direction, class by class in the degrid direction (degrid_cell).
+// Pass A transforms along s and writes (reads, in the degrid direction) the
+// intermediate [t][q / 16][r / 16][16 q][16 r] in segments of up to 16 consecutive
+// r, pass B transforms its whole lines along r (q is the image row).  Image rows
+// j <-> q and columns i <-> p.  The FFT output bin f of a line maps to image index
+// (f + N/2) mod N' and is kept when below N (Algorithm 5 step 3c); the degrid
+// input places image index p at bin (p - N/2) mod N' (zero padding, Algorithm 6
+// step 3b).
 
 template <typename R, int NP>
 struct FftCfg {
@@ -1771,9 +1773,11 @@ __device__ __forceinline__ int shift_half(int f, int half) {
 // lanes of one wave (no block barrier inside a transform), so that the lines fit
 // in its registers and LDS and leave transposed, in segments of kRows
 // frequencies r: no pass over the intermediate is spent on transposing it.  The
-// classes of a line read the same inputs, which their blocks share in the L2.
-// Bound by latency and VALU issue (about half of the issue slots are used, two
-// blocks of 8 waves per CU).  Wide field (N' = 4096, 49 layers, one pass), with
+// classes of a line read the same inputs, which their blocks share in the L2: of
+// the degrid direction's reads 84 % hit it at N' = 4096 and 93 % at 8192 (eight
+// classes: 18 TB/s through the L2, 3.1 GB of 133 from memory).
+// Bound by latency and VALU issue (vector instructions on 53-69 % of a SIMD's
+// cycles, two blocks of 8 waves per CU).  Wide field (N' = 4096, 49 layers, one pass), with
 // the transpose of the intermediate that a whole-line pass needs: FP32 grid
 // 2.13 -> 1.56 ms, degrid 2.06 -> 1.83; FP64 4.55 -> 2.96 and 4.58 -> 3.43;
 // N' = 3072 FP32 degrid 1.63 -> 0.94.  Rows are dealt to the XCDs in turn: the

@@ -1,16 +1,20 @@
 // C-ABI of the wsgrid library: plans, workspace layout and the launch sequences
 // of Algorithm 5 (grid) and Algorithm 6 (degrid) on one gfx950 device.
 //
-// bin = k_bin_count, scan, k_bin_scatter, k_bin_local_sort (by touch class and
-//       support start), k_tile_occupancy
-// grid_visibilities:   bin -> k_grid_tiles (3-D scatter into the occupied tiles
-//                      of the stack) -> k_grid_fft_a (IFFT along s, crop,
-//                      lines [t][q][r]) -> k_grid_fft_b (IFFT along r, crop,
-//                      w-screen, sum over layers, correction) -> dirty [N][N]
+// bin = k_bin_init, k_bin_count or k_bin_count_direct, scan, k_bin_scatter,
+//       k_bin_local_sort (by touch class, then window or support start),
+//       k_tile_occupancy, scan, k_tile_list (per layer pass where memory is short)
+// grid_visibilities:   bin -> k_grid_tiles_mat or k_grid_tiles (3-D scatter into the
+//                      occupied tiles of the stack) -> k_grid_fft_a (IFFT along s,
+//                      crop, intermediate [t][q / 16][r / 16][16][16]) ->
+//                      k_grid_fft_b (IFFT along r, crop, w-screen, sum over layers,
+//                      correction; with k_map_sum where its layers are split) ->
+//                      dirty [N][N]
 // degrid_visibilities: bin; k_degrid_fft_b (correction, w-screen, pad, FFT
-//                      along p, lines [t][q][r]) ->
+//                      along p, the same intermediate) ->
 //                      k_degrid_fft_a (pad, FFT along q, occupied tiles) ->
-//                      k_degrid_tiles (3-D gather, one part per tile reached) ->
+//                      k_degrid_tiles_mat or k_degrid_tiles (3-D gather, one part
+//                      per tile reached) ->
 //                      k_degrid_finish (sum of parts, phase, fold) -> vis [M]
 // Everything after binning runs once per layer pass when the workspace holds
 // fewer layers than the plan has (k_degrid_finish once, at the end).  Batched
@@ -49,7 +53,7 @@ int fail(int code, const std::string& msg) {
         if (e_ != hipSuccess) return fail(WSG_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-constexpr int kMaxBins = 1 << 25;   // bins over all channels (the bin tables take ~46 bytes per bin, beside the lists of marked tiles)
+constexpr int kMaxBins = 1 << 25;   // bins over all channels (the bin tables take ~46 bytes per bin, a list of marked tiles 128 per tile it covers)
 
 // Workspace of grid_visibilities_noalloc: one file-scope device array, which
 // each device that loads the library holds (its own copy) until the process
