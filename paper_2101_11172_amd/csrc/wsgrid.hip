@@ -286,9 +286,8 @@ int check_call(const wsg_plan* plan, wsg_prec prec, int nch, const int64_t* Mc, 
 
 // The list of the marked tiles among tiles [first, first + n), its bounds for a pass
 // left in the bin counts (free by then).
-void list_tiles(void* ws, const Layout& L, const DevParams& P, int first, int n, int stage, hipStream_t s) {
+void list_tiles(void* ws, const Layout& L, const DevParams& P, int first, int n, hipStream_t s) {
     char* w = static_cast<char*>(ws);
-    StageMark mark(s, stage);
     hipLaunchKernelGGL(k_tile_list, dim3((n + 255) / 256), dim3(256), 0, s, reinterpret_cast<const uint8_t*>(w + L.occ),
                        reinterpret_cast<const uint32_t*>(w + L.tpos), reinterpret_cast<const uint32_t*>(w + L.start),
                        reinterpret_cast<const uint32_t*>(w + L.cls), P, first, n,
@@ -364,8 +363,8 @@ void bin_stage(const wsg_plan* plan, bool grid, int stage, const int64_t* Mc, co
         hipLaunchKernelGGL(k_tile_occupancy, dim3((L.nbins + 255) / 256), dim3(256), 0, s, (const uint32_t*)start,
                            (const uint32_t*)cls, P, occ, rows, mask, count);
         scan(count, tpos, bsums, L.nbins, s);
+        if (L.whole_list) list_tiles(ws, L, P, 0, L.nbins, s);
     }
-    if (L.whole_list) list_tiles(ws, L, P, 0, L.nbins, stage, s);
 }
 
 // Layer passes over the binned records `rec` (grid: scatter, transforms,
@@ -402,7 +401,10 @@ int pass_stage(const wsg_plan* plan, bool grid, const Rec<R>* rec, int64_t M, co
         Q.pl0 = pl0;
         Q.pln = std::min(L.pass_layers, L.last_layer - pl0);
         const int nblocks = L.pass_tiles(Q.pln);
-        if (!L.whole_list) list_tiles(ws, L, P, pl0 / kTileT * P.nbs * P.nbr, nblocks, grid ? 0 : 4, s);
+        if (!L.whole_list) {
+            StageMark mark(s, grid ? 0 : 4);
+            list_tiles(ws, L, P, pl0 / kTileT * P.nbs * P.nbr, nblocks, s);
+        }
         if (grid) {
             {
                 StageMark mark(s, 1);
