@@ -1775,7 +1775,7 @@ __device__ __forceinline__ int shift_half(int f, int half) {
 // frequencies r: no pass over the intermediate is spent on transposing it.  The
 // classes of a line read the same inputs, which their blocks share in the L2: of
 // the degrid direction's reads 84 % hit it at N' = 4096 and 93 % at 8192 (eight
-// classes: 18 TB/s through the L2, 3.1 GB of 133 from memory).
+// classes: 18 TB/s through the L2, 6.3 GB of 133 from memory).
 // Bound by latency and VALU issue (vector instructions on 53-69 % of a SIMD's
 // cycles, two blocks of 8 waves per CU).  Wide field (N' = 4096, 49 layers, one pass), with
 // the transpose of the intermediate that a whole-line pass needs: FP32 grid
